@@ -283,14 +283,13 @@ int fdtd_set_material(fdtd_sim *sim, const int32_t *lo, const int32_t *hi,
  *  variant: 0 = auto (autotuned or default), 1 = two-pass reference
  *           (separate H and E kernels, in place), 2 = fused single pass
  *           (one kernel per step, double-buffered state), 3 = several
- *           leapfrog steps per pass over memory, 4 = (2D) the whole grid
- *           in one workgroup, its state in registers for all the steps of
- *           an fdtd_step call, the two layers of a step separated by
- *           workgroup barriers: grids without CPML or mu_r map, ny <= 1024
- *           and at most 16 rows per band of ny (rounded up to 64) columns
- *           (16384 cells at most, e.g. 128 x 128), at most 64 probes (an
- *           fdtd_step call with more probes runs variant 2's single
- *           steps); the default where it applies.  3D: every tile
+ *           leapfrog steps per pass over memory, 4 = (2D) small grids
+ *           without CPML or mu_r map, ny <= 1024 and at most 16 rows per
+ *           band of ny (rounded up to 64) columns (16384 cells at most,
+ *           e.g. 128 x 128), at most 64 probes (an fdtd_step call with more
+ *           probes runs variant 2's single steps): the workgroup tiles of
+ *           variant 3 below, shape and steps per pass chosen by the
+ *           library; the default where it applies.  3D: every tile
  *           advances two steps in one kernel (state n+1 never leaves the
  *           chip, the x/y-CPML auxiliary values of step n+1 excepted: they
  *           pass through a third state set, allocated on first use, 24 B
@@ -329,8 +328,17 @@ int fdtd_set_material(fdtd_sim *sim, const int32_t *lo, const int32_t *hi,
  *    neighbouring rows and columns it needs; an n not divisible by TB ends
  *    with single steps.  The tiles near a slab run on a second stream of
  *    the library, forked from and joined back to the simulation's stream
- *    within each pass.  The default chunk depends on the grid (16-32 rows
- *    where the interior tiles then fill the device once, else 4 or 8).
+ *    within each pass.
+ *    2D workgroup tiles (variant 3 on a 2D grid, tile[0] = 64: 64 columns
+ *    per tile): tile[1] = size class (0: tiles of 32 rows, 1: 64, 2: up to
+ *    96), tile[2] = TB, most leapfrog steps per pass (1 .. 15; 0 = 4),
+ *    tile[3] = 0.  A workgroup holds its tile's state in registers for all
+ *    steps of the pass and recomputes a halo of TB cells; one launch per
+ *    pass; the n steps of a call are split into passes of nearly equal
+ *    length, and a grid that fits one tile takes them all in one.  A call
+ *    of one step runs the single-step kernel, with the same bits.  The
+ *    default for 2D grids (not for grids of less than 40 rows and 1.5 M
+ *    cells or more, and ny up to 2^20).
  * FDTD_EINVAL for unknown or unsupported combinations. */
 typedef struct {
     int32_t variant;

@@ -135,12 +135,11 @@ extern "C" int fdtd_adjoint_grads(fdtd_sim *sim, int64_t T, int64_t n0, int64_t 
         saved = s.kcfg;
         restore_cfg = true;
         if ((s.kcfg.variant != 2 && s.kcfg.variant != 3) || !s.kcfg_explicit) default_variant_tiles(s, s.kcfg);
-        if (s.kcfg.variant == 4) {  // one-workgroup default (no per-step captures): single steps
-            const Fused2DCfg c = default_single2d(s.nx, s.ny);
+        if (s.kcfg.variant == 4) {  // small grid: the same tiles, whatever the number of probes
             s.kcfg = fdtd_kernel_config{};
-            s.kcfg.variant = 2;
-            s.kcfg.tile[0] = c.V;
-            s.kcfg.tile[1] = c.TX;
+            s.kcfg.variant = 3;
+            s.kcfg.tile[0] = 64;
+            wg2d_default(s.nx, s.ny, s.mat(), s.cus, s.kcfg.tile[1], s.kcfg.tile[2]);
             s.kcfg.tb = 1;
         }
         if (s.kcfg.variant != 2 && s.kcfg.variant != 3) fail(FDTD_EINVAL, "no fused 2D kernel for this grid");
@@ -175,6 +174,14 @@ extern "C" int fdtd_adjoint_grads(fdtd_sim *sim, int64_t T, int64_t n0, int64_t 
         // design values of each step at (step - k0) * nd
         auto run = [&](int64_t k0, int64_t k1, const CapArgs *cap) {
             for (int64_t k = k0; k < k1;) {
+                if (s.wg2d()) {
+                    const int m = (int)std::min<int64_t>(s.wg_most(), k1 - k);
+                    s.launch_wg2d(k, m, cap);
+                    k += m;
+                    s.n_done += m;
+                    s.n_rec += m;
+                    continue;
+                }
                 if (multi && k + TB <= k1) {
                     s.launch_tb2d(k, cap);
                     k += TB;

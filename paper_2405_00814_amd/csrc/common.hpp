@@ -170,17 +170,61 @@ struct CapArgs {
 hipError_t launch_2d_tb(const Prob2D &p, const Prob2D *probs_dev, const Tile2T *tiles, int ntiles, bool pml,
                         int mat, const ProbeTiles &pt, int V, int TB, const int64_t *step_base, int64_t step,
                         hipStream_t st, const CapArgs *capture = nullptr);
+
+// 2D, several steps per pass, one workgroup per tile of 64 columns, the
+// tile's state in registers (k2dw.hpp).  Loaded: rows from a, columns from
+// c; written: rows [i0, i1), columns [j0, j1).  kind: 0 = neither walls nor
+// slab cells nor cells outside the grid, 1 = no slab cells, 2 = any.
+struct TileW {
+    int prob, kind, i0, i1, j0, j1, a, c;
+};
+// Monitor samples of a pass: step s of the pass writes the box cells'
+// values of one component to ring row s.
+struct TapArgs {
+    int comp, i0, i1, j0, j1;
+    int64_t npts;
+    float *ring;
+};
+struct WgArgs {
+    Prob2D p;
+    const Prob2D *probs;       // nullptr: one problem p, step = `step`
+    const TileW *tiles;
+    int ntiles, nsteps;
+    ProbeTiles pt;
+    const int64_t *step_base;  // with probs: step = *step_base + step
+    int64_t step;
+    CapArgs cap;
+    TapArgs tap;
+};
+// Tile rows by size class and material maps: of tiles without slab cells,
+// with x-slab rows or y-slab columns, with both.
+struct WgShape {
+    int none, one, both;
+};
+constexpr int kWgClasses = 3;
+constexpr WgShape wg2d_shape(int cls, int mat) {
+    return cls == 0 ? WgShape{32, 32, 32}
+         : cls == 1 ? WgShape{64, 64, 64}
+         : mat == 0 ? WgShape{96, 56, 40}
+         : mat == 1 ? WgShape{80, 48, 36}
+                    : WgShape{64, 40, 32};
+}
+// (sx, sy: rows and columns of the x and y slabs)
+bool wg2d_supported(int ny, int sx, int sy, int cls, int TB);
+// tiles of one problem for passes of at most TB steps, ordered by rows
+void wg2d_plan(int prob, int nx, int ny, int cls, int mat, int TB, const int *xlohi, const int *ylohi,
+               std::vector<TileW> &tiles);
+// size class and steps per pass for a grid on `cus` compute units
+void wg2d_default(int nx, int ny, int mat, int cus, int &cls, int &TB);
+// xt: 0 plain, 1 with a.cap, 2 with a.tap (single problem only)
+hipError_t launch_2d_wg(const WgArgs &a, int cls, int mat, int xt, hipStream_t st);
 int fused2d_ntiles(int nx, int ny, const Fused2DCfg &c);
 int fused2d_tile_of(int nx, int ny, const Fused2DCfg &c, int i, int j);
 bool fused2d_supported(int nx, int ny, const Fused2DCfg &c);
 
-// Whole 2D grid in one workgroup (kernel variant 4): no CPML, no mu_r map
-// (mat 0 or 1), at most 16
-// rows per band of ny (rounded up to 64) columns in 1024 threads, at most
-// 64 probes; the state in registers for all nsteps steps (s0 in, s1 out;
-// several launches for more than 65536 steps).
+// Kernel variant 4's grids: no CPML, no mu_r map, at most 16 rows per band
+// of ny (rounded up to 64) columns over 1024 lanes, at most 64 probes.
 bool res2d_supported(int nx, int ny, bool cpml, int np);
-hipError_t launch_2d_resident(const Prob2D &p, int mat, int64_t step, int64_t nsteps, hipStream_t st);
 hipError_t launch_3d_ref(const Prob3D &p, int64_t step, hipStream_t st);
 // rec[slot[q]][step - rec_base] = p.s0 component probe_comp at cell[q], q < n
 hipError_t launch_3d_probe_list(const Prob3D &p, const int *cell, const int *slot, int n, int64_t step,

@@ -19,6 +19,22 @@ __device__ __forceinline__ float lane_prev(float x) {
     return __int_as_float(__builtin_amdgcn_update_dpp(i, i, 0x138 /* wave_shr:1 */, 0xf, 0xf, false));
 }
 
+// The 2D update of one H component, h +- Db (k d + psi), in the workgroup
+// tiles' sequence of roundings (k2dw.hpp; sgn = +-1): with a Db map the
+// bracket first; else the difference with its weight w = Db k in one fused
+// multiply-add, then the CPML value where the cell has one.
+__device__ __forceinline__ float h_next(float h, float sgn, float db, float w, float k, float d, bool map, bool in,
+                                        float psi) {
+#pragma clang fp contract(off)
+    if (map) {
+        float t = d * k;
+        if (in) t += psi;
+        return __builtin_fmaf(sgn * db, t, h);
+    }
+    h = __builtin_fmaf(sgn * w, d, h);
+    return in ? __builtin_fmaf(sgn * db, psi, h) : h;
+}
+
 // V consecutive floats (V = 1, 2, 4) as one aligned vector access.
 template <int V>
 __device__ __forceinline__ void ldv(float (&r)[V], const float *p) {

@@ -138,6 +138,9 @@ __device__ __forceinline__ void fused2d_tile(const Prob2D &p, int TX, int cx, in
                                              const ProbeTiles &pt, int pbeg, int pend,
                                              int64_t step, int4 design, float *cap_ez,
                                              float *cap_br) {
+// fused multiply-adds written out, in the workgroup tiles' order (k2dw.hpp):
+// a call's steps give the same bits through either kernel
+#pragma clang fp contract(off)
     const int lane = threadIdx.x & 63;
     const int nx = p.nx, ny = p.ny;
     const int x0 = cx * TX, x1 = min(x0 + TX, nx);
@@ -205,9 +208,9 @@ __device__ __forceinline__ void fused2d_tile(const Prob2D &p, int TX, int cx, in
 #pragma unroll
         for (int v = 0; v < V; ++v) {
             const float dEx = ez_c[v] - ez_m[v];
-            float tx = dEx * kHx;
-            if (PML && ii >= 0) tx += p.x.bH[i] * ps_o[v] + p.x.cH[i] * dEx;
-            hy_p[v] = hy_o[v] + db[v] * tx;
+            const bool in = PML && ii >= 0;
+            const float ps = in ? __builtin_fmaf(p.x.cH[i], dEx, p.x.bH[i] * ps_o[v]) : 0.f;
+            hy_p[v] = h_next(hy_o[v], 1.f, db[v], p.db0 * kHx, kHx, dEx, mumap, in, ps);
         }
     }
 
@@ -258,21 +261,17 @@ __device__ __forceinline__ void fused2d_tile(const Prob2D &p, int TX, int cx, in
 #pragma unroll
         for (int v = 0; v < V; ++v) {
             const float dEy = ez_r[v] - ez_c[v];
-            float ty = dEy * kHy[v];
-            if (PML && jj[v] >= 0) {
+            const bool iny = PML && jj[v] >= 0, inx = PML && ii >= 0;
+            float psy = 0.f;
+            if (iny) {
                 const int64_t q = (int64_t)i * syw + jj[v];
-                const float ps = bHy[v] * p.s0.psi_hx[q] + cHy[v] * dEy;
-                p.s1.psi_hx[q] = ps;
-                ty += ps;
+                psy = __builtin_fmaf(cHy[v], dEy, bHy[v] * p.s0.psi_hx[q]);
+                p.s1.psi_hx[q] = psy;
             }
-            hx_n[v] = hx_o[v] - db[v] * ty;
+            hx_n[v] = h_next(hx_o[v], -1.f, db[v], p.db0 * kHy[v], kHy[v], dEy, mumap, iny, psy);
             const float dEx = ez_n[v] - ez_c[v];
-            float tx = dEx * kHx;
-            if (PML && ii >= 0) {
-                psx_n[v] = p.x.bH[i] * psx_o[v] + p.x.cH[i] * dEx;
-                tx += psx_n[v];
-            }
-            hy_n[v] = hy_o[v] + db[v] * tx;
+            psx_n[v] = inx ? __builtin_fmaf(p.x.cH[i], dEx, p.x.bH[i] * psx_o[v]) : 0.f;
+            hy_n[v] = h_next(hy_o[v], 1.f, db[v], p.db0 * kHx, kHx, dEx, mumap, inx, psx_n[v]);
         }
         if (PML && ii >= 0 && valid) stv<V>(p.s1.psi_hy + (int64_t)ii * ny + jb, psx_n);
 
@@ -288,10 +287,9 @@ __device__ __forceinline__ void fused2d_tile(const Prob2D &p, int TX, int cx, in
                 const float hxo = p.s0.hx[row + jm];
                 const float dbm = mumap ? p.db[row + jm] : p.db0;
                 const float dEy = ez_c[0] - ez_mm;
-                float ty = dEy * kHy_m;
-                if (PML && jj_m >= 0)
-                    ty += bHy_m * p.s0.psi_hx[(int64_t)i * syw + jj_m] + cHy_m * dEy;
-                shl = hxo - dbm * ty;
+                const bool in = PML && jj_m >= 0;
+                const float ps = in ? __builtin_fmaf(cHy_m, dEy, bHy_m * p.s0.psi_hx[(int64_t)i * syw + jj_m]) : 0.f;
+                shl = h_next(hxo, -1.f, dbm, p.db0 * kHy_m, kHy_m, dEy, mumap, in, ps);
             }
         }
         hx_l[0] = shl;
@@ -308,20 +306,18 @@ __device__ __forceinline__ void fused2d_tile(const Prob2D &p, int TX, int cx, in
             if (i >= 1 && j >= 1) {
                 const float dHy = hy_n[v] - hy_p[v];
                 const float dHx = hx_n[v] - hx_l[v];
-                float tx = dHy * kEx;
-                float ty = dHx * kEy[v];
+                float br = __builtin_fmaf(-kEy[v], dHx, kEx * dHy);
                 if (PML && ii >= 0) {
-                    pex_n[v] = p.x.bE[i] * pex_o[v] + p.x.cE[i] * dHy;
-                    tx += pex_n[v];
+                    pex_n[v] = __builtin_fmaf(p.x.cE[i], dHy, p.x.bE[i] * pex_o[v]);
+                    br += pex_n[v];
                 }
                 if (PML && jj[v] >= 0) {
                     const int64_t q = (int64_t)i * syw + jj[v];
-                    const float ps = bEy[v] * p.s0.psi_ezy[q] + cEy[v] * dHx;
+                    const float ps = __builtin_fmaf(cEy[v], dHx, bEy[v] * p.s0.psi_ezy[q]);
                     if (valid) p.s1.psi_ezy[q] = ps;
-                    ty += ps;
+                    br -= ps;
                 }
-                const float br = tx - ty;
-                ez_w[v] = (lossy ? ca[v] * ez_c[v] : ez_c[v]) + cb[v] * br;
+                ez_w[v] = __builtin_fmaf(cb[v], br, lossy ? ca[v] * ez_c[v] : ez_c[v]);
                 if (CAPTURE && valid && i >= design.x && i < design.y && j >= design.z &&
                     j < design.w) {
                     const int64_t q = (int64_t)(i - design.x) * (design.w - design.z) + (j - design.z);

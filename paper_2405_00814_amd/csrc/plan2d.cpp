@@ -60,4 +60,93 @@ void tb2d_plan(int prob, int nx, int ny, int V, int TB, int TX, int TXo, const i
     }
 }
 
+// ---------------------------------------------------------------------------
+// Workgroup tiles (k2dw.hpp)
+// ---------------------------------------------------------------------------
+bool wg2d_supported(int ny, int sx, int sy, int cls, int TB) {
+    // byte offsets of a tile's rows and of the x slabs' rows fit 31 bits; a
+    // tile keeps cells to write
+    return ny >= 3 && ny <= (1 << 20) && (int64_t)sx * ny < (1 << 29) && sy <= (1 << 20) && cls >= 0 && cls < kWgClasses && TB >= 1 && TB <= 15 &&
+           wg2d_shape(cls, 2).both > 2 * TB;
+}
+
+bool res2d_supported(int nx, int ny, bool cpml, int np) {
+    if (cpml || nx < 1 || ny < 1 || ny > 1024 || np > 64) return false;
+    const int bands = 1024 / ((ny + 63) / 64 * 64);
+    return (nx + bands - 1) / bands <= 16;
+}
+
+// Measured over 64^2 .. 6400^2 on 256 CUs (us per step): tiles of 32 rows
+// while there are at most two per CU at 12 steps per pass (250^2 1.18
+// against 1.70 with 64 rows, 400^2 1.43 against 1.61), then 64 rows up to
+// about two per CU (1024^2 2.42 against 2.46 with 96 rows and 3.0 with 32),
+// then 96 (2048^2 4.8 against 6.0).  More steps per pass cost halo and save
+// launches: 14 while all tiles run at once, 12, or 10 where 12 would start
+// another round (1024^2: 10 steps 2.42, 12 steps 2.79; 4096^2: 12 steps
+// 14.3, 8 steps 18.0; with a Db map, 64-row tiles, 10 steps 20.1, 12 20.8).
+void wg2d_default(int nx, int ny, int mat, int cus, int &cls, int &TB) {
+    auto along = [](int n, int h, int tb) { return n <= h ? 1 : 2 + std::max(0, (n - 2 * (h - tb) + h - 2 * tb - 1) / (h - 2 * tb)); };
+    auto count = [&](int h, int tb) { return (int64_t)along(nx, h, tb) * along(ny, 64, tb); };
+    if (count(32, 12) <= 2 * (int64_t)cus) {
+        cls = 0;
+        TB = count(32, 14) <= cus ? 14 : 12;
+        return;
+    }
+    if (count(64, 10) * 4 <= 9 * (int64_t)cus) {
+        cls = 1;
+        for (TB = 14; TB > 10 && count(64, TB) * 10 > 21 * (int64_t)cus;) TB -= 2;
+        return;
+    }
+    cls = 2;
+    TB = mat == 2 ? 10 : 12;
+}
+
+void wg2d_plan(int prob, int nx, int ny, int cls, int mat, int TB, const int *xlohi, const int *ylohi,
+               std::vector<TileW> &tiles) {
+    const WgShape sh = wg2d_shape(cls, mat);
+    const int xlo = xlohi[0], xhi = xlohi[1], ylo = ylohi[0], yhi = ylohi[1];
+    std::vector<TileW> t;
+    for (int j0 = 0; j0 < ny;) {
+        const int c = j0 > 0 ? j0 - TB : 0;
+        const int j1 = c + 64 >= ny ? ny : c + 64 - TB;
+        // the strip's loaded columns: slab cells, walls or ghosts
+        const bool py = (ylo > 0 && c < ylo) || (yhi > 0 && c + 64 > ny - yhi);
+        const bool ey = c == 0 || c + 64 > ny;
+        for (int i0 = 0; i0 < nx;) {
+            int a = i0 > 0 ? i0 - TB : 0;
+            // kind and height of a tile loading rows from a
+            auto slab = [&](int rows) { return (xlo > 0 && a - 1 < xlo) || (xhi > 0 && a + rows > nx - xhi); };
+            int kind, rows = py ? sh.one : sh.none;
+            if (!slab(rows)) {
+                kind = py ? 2 : (ey || a == 0 || a + rows > nx ? 1 : 0);
+            } else {
+                // a tile that would reach into the last slab is moved up to
+                // end before it, where that leaves it at least half its rows
+                const int a2 = nx - xhi - rows;
+                if (xhi > 0 && a2 < a && a2 >= 1 && a2 - 1 >= xlo && a2 + rows - TB - i0 >= (rows - 2 * TB) / 2) {
+                    a = a2;
+                    kind = py ? 2 : (ey ? 1 : 0);
+                } else {
+                    rows = py ? sh.both : sh.one;
+                    kind = py ? 4 : 3;
+                    // (with the smaller height the slab may be out of reach)
+                    if (!slab(rows)) kind = py ? 2 : (ey || a == 0 || a + rows > nx ? 1 : 0);
+                    if (kind < 3) rows = py ? sh.one : sh.none;
+                    if (kind < 3 && slab(rows)) {
+                        rows = py ? sh.both : sh.one;
+                        kind = py ? 4 : 3;
+                    }
+                }
+            }
+            const int i1 = a + rows >= nx ? nx : a + rows - TB;
+            t.push_back(TileW{prob, kind, i0, i1, j0, j1, a, c});
+            i0 = i1;
+        }
+        j0 = j1;
+    }
+    // rows together: neighbouring strips share their halo rows' lines
+    std::stable_sort(t.begin(), t.end(), [](const TileW &u, const TileW &v) { return u.i0 < v.i0; });
+    tiles.insert(tiles.end(), t.begin(), t.end());
+}
+
 }  // namespace gem

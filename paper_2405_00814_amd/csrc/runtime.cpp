@@ -479,7 +479,36 @@ void Sim::build_probe_tiles() {
     pt_cfg[3] = c3;
     pt_cfg[4] = vm;
     pt_cfg[5] = kcfg.tile[3];
-    if (ndim == 2 && kcfg.variant == 3) {
+    if (wg2d()) {
+        const int xl[2] = {ax[0].lo, ax[0].hi}, yl[2] = {ax[1].lo, ax[1].hi};
+        std::vector<TileW> tl;
+        if (kcfg.variant == 4) {
+            wg2d_default(nx, ny, mat, cus, wg_cls, wg_tb);
+        } else {
+            wg_cls = kcfg.tile[1];
+            wg_tb = kcfg.tile[2];
+        }
+        wg2d_plan(0, nx, ny, wg_cls, mat, wg_tb, xl, yl, tl);
+        wg_n = (int)tl.size();
+        swap_in(wg_dev, dev_upload(al, tl.data(), tl.size(), st));
+        std::vector<std::pair<int, int>> ent;  // (owning tile, probe)
+        for (size_t q = 0; q < probe_cells.size(); ++q) {
+            const int i = (int)(probe_cells[q] / ny), j = (int)(probe_cells[q] % ny);
+            for (size_t t = 0; t < tl.size(); ++t)
+                if (i >= tl[t].i0 && i < tl[t].i1 && j >= tl[t].j0 && j < tl[t].j1) ent.push_back({(int)t, (int)q});
+        }
+        std::stable_sort(ent.begin(), ent.end());
+        std::vector<int> st2(tl.size() + 1, 0), ce, sl;
+        for (auto &e : ent) {
+            ce.push_back((int)probe_cells[(size_t)e.second]);
+            sl.push_back(e.second);
+            st2[(size_t)e.first + 1]++;
+        }
+        for (size_t t = 0; t < tl.size(); ++t) st2[t + 1] += st2[t];
+        swap_in(pt2_start, dev_upload(al, st2.data(), st2.size(), st));
+        swap_in(pt2_cell, dev_upload(al, ce.data(), std::max<size_t>(ce.size(), 1), st));
+        swap_in(pt2_slot, dev_upload(al, sl.data(), std::max<size_t>(sl.size(), 1), st));
+    } else if (ndim == 2 && kcfg.variant == 3) {
         const int V = kcfg.tile[0], TX = kcfg.tile[1], TB = kcfg.tile[2];
         const int xl[2] = {ax[0].lo, ax[0].hi}, yl[2] = {ax[1].lo, ax[1].hi};
         std::vector<Tile2T> in, out;
@@ -551,24 +580,50 @@ void Sim::launch_tb2d(int64_t step, const CapArgs *cap) {
 }
 
 
+// nsteps (at most wg_most()) steps of the 2D grid in one pass of workgroup
+// tiles: one launch over all of them.
+void Sim::launch_wg2d(int64_t step, int nsteps, const CapArgs *cap, const TapArgs *tap) {
+    WgArgs a{};
+    a.p = prob2d(cur, 1 - cur);
+    a.tiles = wg_dev;
+    a.ntiles = wg_n;
+    a.nsteps = nsteps;
+    if (!probe_cells.empty()) a.pt = ProbeTiles{pt2_start, pt2_cell, pt2_slot};
+    a.step = step;
+    if (cap) a.cap = *cap;
+    if (tap) a.tap = *tap;
+    hip_check(launch_2d_wg(a, wg_cls, mat(), cap ? 1 : (tap ? 2 : 0), st), "2d workgroup tiles");
+    cur = 1 - cur;
+    last_launches += 1;
+}
+
+// Phase factors of the next n ring rows (steps `step` .. step + n - 1);
+// returns the first of them.  n must not pass the ring's end.
+int Sim::dft_rows(int64_t step, int n) {
+    const int r0 = dft.nbuf;
+    for (int k = 0; k < n; ++k) {
+        const double t = ((double)(step + k) + (dft.comp >= FDTD_HX ? 0.5 : 1.0)) * dt;
+        for (int q = 0; q < dft.nf; ++q) {
+            const double a = 2.0 * kPi * dft.f[q] * t;
+            dft.pend.re[r0 + k][q] = std::cos(a) * dt;
+            dft.pend.im[r0 + k][q] = -std::sin(a) * dt;
+        }
+    }
+    dft.nbuf = r0 + n;
+    dft.nacc += n;
+    return r0;
+}
+
 // After step `step` (state step+1): the monitor's sums gain the field
 // sample times exp(-2 pi i f t) dt, t = (step+1) dt for E and (step+1/2) dt
 // for H (the sample's time on the leapfrog grid).
 // The sample goes to the next row of the ring with its phase factors; a
 // full ring is summed.
 void Sim::dft_accumulate(int64_t step) {
-    const int r = dft.nbuf;
-    const double t = ((double)step + (dft.comp >= FDTD_HX ? 0.5 : 1.0)) * dt;
-    for (int q = 0; q < dft.nf; ++q) {
-        const double a = 2.0 * kPi * dft.f[q] * t;
-        dft.pend.re[r][q] = std::cos(a) * dt;
-        dft.pend.im[r][q] = -std::sin(a) * dt;
-    }
+    const int r = dft_rows(step, 1);
     const float *fld = is_graph ? g.x : f[cur][dft.comp];
     const DftBox box{dft.box[0], dft.box[2], dft.box[4], dft.box[3] - dft.box[2], dft.box[5] - dft.box[4], ny, nz};
     hip_check(launch_dft_gather(fld, dft.idx, box, dft.npts, dft.ring + (int64_t)r * dft.npts, st), "dft");
-    dft.nbuf = r + 1;
-    dft.nacc += 1;
     last_launches += 1;
     if (dft.nbuf == kDftBatch) {
         dft_flush();
@@ -764,18 +819,32 @@ void Sim::advance(int64_t n) {
     // a frequency-domain monitor needs every step's field: single steps
     const bool mon = dft.comp >= 0;
     const bool two = kcfg.variant == 3 && ndim == 3 && !is_graph && !mon;
-    const bool tb2 = kcfg.variant == 3 && ndim == 2 && !is_graph && !mon;
+    const bool wg = wg2d() && n > 1;
+    const bool tb2 = kcfg.variant == 3 && ndim == 2 && !is_graph && !mon && !wg2d();
     const int64_t inc = probe_cells.empty() ? 0 : 1;
     int64_t q = 0;
-    // whole grid in one workgroup: all n steps in one launch (single steps
-    // where the probes no longer fit it)
-    if (kcfg.variant == 4 && ndim == 2 && !is_graph && !mon && n > 0 && res2d_ok()) {
-        hip_check(launch_2d_resident(prob2d(cur, 1 - cur), mat(), n_done, n, st), "2d resident steps");
-        cur = 1 - cur;
-        n_done += n;
-        n_rec += n * inc;
-        last_launches += (n + 65535) / 65536;
-        return;
+    // workgroup tiles: the steps in passes of nearly equal length (a single
+    // step is left to the single-step kernel: 6.3 us on 250^2 against 7.7);
+    // with a monitor the tiles write their samples of every step to its
+    // ring, and a pass ends where the ring does
+    while (wg && q < n) {
+        const int64_t left = n - q, TB = wg_most(), np = (left + TB - 1) / TB;
+        int k = (int)((left + np - 1) / np);
+        if (mon) {
+            k = std::min(k, kDftBatch - dft.nbuf);
+            const TapArgs tap{dft.comp, dft.box[0], dft.box[1], dft.box[2], dft.box[3], dft.npts,
+                              dft.ring + (int64_t)dft_rows(n_done, k) * dft.npts};
+            launch_wg2d(n_done, k, nullptr, &tap);
+            if (dft.nbuf == kDftBatch) {
+                dft_flush();
+                last_launches += 1;
+            }
+        } else {
+            launch_wg2d(n_done, k);
+        }
+        n_done += k;
+        n_rec += k * inc;
+        q += k;
     }
     if (two)
         for (; q + 2 <= n; q += 2) {
@@ -897,8 +966,18 @@ int default_variant_tiles(const Sim &s, fdtd_kernel_config &k) {
         return 0;
     }
     if (s.ndim == 2) {
-        if (!s.is_graph && s.res2d_ok()) {  // small grid without CPML: one workgroup
+        if (!s.is_graph && s.res2d_ok()) {  // small grid without CPML
             k.variant = 4;
+            return 0;
+        }
+        int cls, wtb;
+        wg2d_default(s.nx, s.ny, s.mat(), s.cus, cls, wtb);
+        const bool strip = s.nx < 40 && s.ncell >= kTB2MinCells;  // a tile's rows would lie mostly outside
+        if (!strip && wg2d_supported(s.ny, s.ax[0].lo + s.ax[0].hi, s.ax[1].lo + s.ax[1].hi, cls, wtb)) {
+            k.variant = 3;
+            k.tile[0] = 64;
+            k.tile[1] = cls;
+            k.tile[2] = wtb;
             return 0;
         }
         const int vt = 1, tx = tb2d_default_tx(s.nx, s.ny, vt, s.cus);
@@ -936,7 +1015,7 @@ int default_variant_tiles(const Sim &s, fdtd_kernel_config &k) {
 static bool config_ok(const Sim &s, const fdtd_kernel_config &k) {
     // tb: 0 or 1; for 2D multi-step passes also the steps per replayed graph
     // (an even number of passes, at most 1024 steps)
-    const bool graph_tb = s.ndim == 2 && k.variant == 3 && k.tile[2] > 0 && k.tb >= 2 * k.tile[2] && k.tb <= 1024 &&
+    const bool graph_tb = s.ndim == 2 && k.variant == 3 && k.tile[0] != 64 && k.tile[2] > 0 && k.tb >= 2 * k.tile[2] && k.tb <= 1024 &&
                           k.tb % (2 * k.tile[2]) == 0 && !s.is_graph;
     if (k.tb != 0 && k.tb != 1 && !graph_tb) return false;
     if (k.variant == 1) return true;
@@ -947,6 +1026,7 @@ static bool config_ok(const Sim &s, const fdtd_kernel_config &k) {
     if (k.variant != 2 && k.variant != 3) return false;
     if (s.ndim == 2) {
         if (k.variant == 2) return fused2d_supported(s.nx, s.ny, Fused2DCfg{k.tile[0], k.tile[1]});
+        if (k.tile[0] == 64) return k.tile[3] == 0 && wg2d_supported(s.ny, s.ax[0].lo + s.ax[0].hi, s.ax[1].lo + s.ax[1].hi, k.tile[1], k.tile[2]);
         return k.tile[3] >= 0 && k.tile[3] <= 65536 && tb2d_supported(s.ny, k.tile[0], k.tile[2], k.tile[1]) &&
                fused2d_supported(s.nx, s.ny, default_single2d(s.nx, s.ny));
     }
@@ -1413,9 +1493,9 @@ int fdtd_step_profile(fdtd_sim *sim, int32_t steps, fdtd_launch_stat *out, int32
     const bool fused3 = s.ndim == 3 && !s.is_graph && s.kcfg.variant >= 2;
     const bool two = fused3 && s.kcfg.variant == 3 && steps >= 2;
     const bool tb2 = s.ndim == 2 && !s.is_graph && s.kcfg.variant == 3 && steps >= s.kcfg.tile[2];
-    const bool res = s.ndim == 2 && !s.is_graph && s.kcfg.variant == 4 && s.res2d_ok();
+    const bool res = s.kcfg.variant == 4 && s.wg2d();
     // one timed unit: a step, a pair of steps for the 3D two-step pass, the
-    // TB steps of the 2D multi-step pass, or all steps (one workgroup)
+    // TB steps of the 2D multi-step pass, or all steps (variant 4)
     const int32_t per = two ? 2 : (tb2 ? s.kcfg.tile[2] : (res ? steps : 1));
     const int32_t units = steps / per;
     const size_t nl = two ? s.pair_launches() : (fused3 ? s.plan3.l.size() : 1);
@@ -1440,13 +1520,16 @@ int fdtd_step_profile(fdtd_sim *sim, int32_t steps, fdtd_launch_stat *out, int32
             s.launch_pair(s.n_done, e);
         } else if (tb2) {
             hip_check(hipEventRecord(e[0], s.st), "event");
-            s.launch_tb2d(s.n_done);
+            if (s.wg2d()) s.launch_wg2d(s.n_done, per);
+            else s.launch_tb2d(s.n_done);
             hip_check(hipEventRecord(e[1], s.st), "event");
         } else if (res) {
             hip_check(hipEventRecord(e[0], s.st), "event");
-            hip_check(launch_2d_resident(s.prob2d(s.cur, 1 - s.cur), s.mat(), s.n_done, per, s.st), "2d resident steps");
-            s.cur = 1 - s.cur;
-            s.last_launches += (per + 65535) / 65536;
+            for (int32_t d = 0; d < per;) {
+                const int m = std::min(per - d, s.wg_most());
+                s.launch_wg2d(s.n_done + d, m);
+                d += m;
+            }
             hip_check(hipEventRecord(e[1], s.st), "event");
         } else {
             if (fused3) s.lev = e;
@@ -1906,7 +1989,7 @@ int fdtd_set_kernel(fdtd_sim *sim, const fdtd_kernel_config *cfg) {
         default_variant_tiles(s, k);
     } else if (s.ndim == 2 && k.variant == 3) {
         if (k.tile[0] == 0) k.tile[0] = 1;
-        if (k.tile[1] == 0) k.tile[1] = kTB2DefaultTX;
+        if (k.tile[1] == 0 && k.tile[0] != 64) k.tile[1] = kTB2DefaultTX;
         if (k.tile[2] == 0) k.tile[2] = 4;
     } else if (s.ndim == 2 && k.variant == 2) {
         const Fused2DCfg c = default_single2d(s.nx, s.ny);
@@ -1972,6 +2055,16 @@ int fdtd_autotune(fdtd_sim *sim, int32_t trial_steps, fdtd_kernel_config *out) {
             k.tb = 1;
             if (config_ok(s, k)) cand.push_back(k);
         }
+        for (int cls = 0; cls < kWgClasses; ++cls)
+            for (int TB : {8, 10, 12, 14}) {
+                fdtd_kernel_config k{};
+                k.variant = 3;
+                k.tile[0] = 64;
+                k.tile[1] = cls;
+                k.tile[2] = TB;
+                k.tb = 1;
+                if (config_ok(s, k)) cand.push_back(k);
+            }
         for (int V : {1, 2, 4})
             for (int TX : {4, 8, 16, 32}) {
                 fdtd_kernel_config k{};

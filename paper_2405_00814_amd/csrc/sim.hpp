@@ -126,9 +126,19 @@ struct Sim {
     Tile2T *tb2_dev = nullptr;
     int tb2_inner = 0, tb2_outer = 0;
     int *pt2_start = nullptr, *pt2_cell = nullptr, *pt2_slot = nullptr;
+    // 2D, steps of a pass in workgroup tiles (variant 3 with tile[0] = 64:
+    // tile[1] = size class, tile[2] = most steps per pass; variant 4): the
+    // tile list and its probe groups (pt2_*)
+    TileW *wg_dev = nullptr;
+    int wg_n = 0, wg_cls = 0, wg_tb = 1;
+    bool wg2d() const {
+        return ndim == 2 && !is_graph && ((kcfg.variant == 3 && kcfg.tile[0] == 64) || (kcfg.variant == 4 && res2d_ok()));
+    }
+    // most steps per pass: a grid in one tile has no halo to use up
+    int wg_most() const { return wg_n == 1 ? 65536 : wg_tb; }
     int mat() const { return mumap ? 2 : (lossy ? 1 : 0); }
-    // the 2D grid (no CPML, split field, mu_r map or graph) fits the
-    // one-workgroup kernel with the current probes
+    // variant 4 takes the 2D grid (no CPML, split field, mu_r map or graph)
+    // with the current probes
     bool res2d_ok() const {
         return ndim == 2 && !split && !is_graph && mat() <= 1 &&
                res2d_supported(nx, ny, ax[0].lo + ax[0].hi + ax[1].lo + ax[1].hi > 0, (int)probe_cells.size());
@@ -229,6 +239,8 @@ struct Sim {
     void records_to_host(float *out, int64_t ld, int64_t m);
     void split_check() const;
     void launch_tb2d(int64_t step, const CapArgs *cap = nullptr);
+    void launch_wg2d(int64_t step, int nsteps, const CapArgs *cap = nullptr, const TapArgs *tap = nullptr);
+    int dft_rows(int64_t step, int n);
     void advance(int64_t n);
     void alloc_set(int set);
     void zero_state();

@@ -1,0 +1,127 @@
+"""GPU parity of the 2D workgroup-tile stepper (kernel variant 3 with tile[0] =
+64): every size class and 1 to 15 steps per pass give the bits of the
+single-step stepper (variant 2), which the other tests hold to the oracle,
+and the oracle's fields within relative L2 1e-4."""
+import numpy as np
+import pytest
+
+from paper_2405_00814_amd import workloads as W
+
+from helpers import rel_l2
+
+pytestmark = pytest.mark.gpu
+
+
+def _problem(shape, npml, mat, steps=33):
+    """Random state problem; mat 0: Cb map, 1: Ca too, 2: Db too; probes on
+    tile and wavefront seams; a source box across a tile seam."""
+    nx, ny = shape
+    pb = W.dielectric2d(nx, ny=ny, steps=steps, seed=1, nrect=6, side=(4, 24), npml=max(npml), nprobes=1,
+                        lossy=mat >= 1)
+    pb.npml = npml
+    pb.cpml = dict(m=3.0, sigma_max=0.0, kappa_max=3.0, alpha_max=0.05, m_alpha=1.0)
+    if mat == 2:
+        pb.mu_r = np.random.default_rng(2).uniform(1, 2, shape).astype(np.float32)
+    c = [(i, j) for i in (0, 1, 7, 8, 15, 16, 31, 32, nx // 2, nx - 1) for j in (0, 1, 48, 49, 63, 64, ny - 1)
+         if i < nx and j < ny]
+    pb.probes = np.array(c, np.int32)
+    pb.source.cell = (max(1, nx // 2 - 3), max(1, ny // 2 - 4))
+    pb.source.hi = (min(nx, nx // 2 + 3), min(ny, ny // 2 + 4))
+    return pb
+
+
+def _state(shape):
+    rng = np.random.default_rng(3)
+    return {f: (rng.standard_normal(shape) * s).astype(np.float32) for f, s in (("ez", 1), ("hx", 1 / 377), ("hy", 1 / 377))}
+
+
+def _run(pb, init, kernel, comp="ez"):
+    from paper_2405_00814_amd.sim import Sim
+    s = Sim.from_problem(pb)
+    s.set_kernel(*kernel)
+    s.set_probes(comp, pb.probes)
+    for f, a in init.items():
+        s.set_field(f, a)
+    for n in (1, 2, pb.steps - 3):
+        s.step(n)
+    out = {f: s.get_field(f) for f in init}
+    out["probe"], out["state"] = s.probe(), s.save_state()[64:]
+    s.close()
+    return out
+
+
+SHAPES = [((3, 5), (0, 0, 0, 0)), ((32, 64), (0, 0, 0, 0)), ((33, 65), (8, 8, 8, 8)), ((97, 130), (0, 12, 9, 0)),
+          ((203, 147), (16, 16, 16, 16)), ((300, 83), (12, 0, 0, 0))]
+
+
+@pytest.mark.parametrize("mat", [0, 1, 2])
+@pytest.mark.parametrize("shape,npml", SHAPES)
+def test_wg2d_bits_of_the_single_step_kernel(shape, npml, mat):
+    from oracle import oracle as O
+    pb = _problem(shape, npml, mat)
+    init = _state(shape)
+    comp = ("ez", "hx", "hy")[mat]
+    one = _run(pb, init, (2,), comp)
+    for cls in (0, 1, 2):
+        for TB in (1, 6, 15):
+            got = _run(pb, init, (3, (64, cls, TB)), comp)
+            for k in one:
+                assert np.array_equal(got[k], one[k], equal_nan=True), (cls, TB, k)
+    o = O.for_problem(pb)
+    o.set_state({f: a.astype(np.float64) for f, a in init.items()})
+    o.run(pb.steps)
+    for f in init:
+        assert rel_l2(one[f], getattr(o, f)) <= 1e-4, f
+
+
+@pytest.mark.parametrize("comp", ["ez", "hx", "hy"])
+def test_wg2d_monitor_bits(comp):
+    """The tiles' monitor samples: the sums of the single-step kernel's."""
+    from paper_2405_00814_amd.sim import Sim
+    pb = _problem((150, 210), (8, 8, 8, 8), 1)
+    init, out = _state(pb.shape), []
+    for kernel in ((2,), (3, (64, 0, 12)), (3, (64, 1, 5)), (3, (64, 2, 15))):
+        s = Sim.from_problem(pb)
+        s.set_kernel(*kernel)
+        for f, a in init.items():
+            s.set_field(f, a)
+        s.set_dft(comp, (3, 5), (149, 200), [1e9, 2.5e9])
+        for n in (1, 5, 30):
+            s.step(n)
+        x, ns = s.get_dft()
+        assert ns == 36
+        out.append(x)
+        s.close()
+    for x in out[1:]:
+        assert np.array_equal(x, out[0])
+
+
+def test_wg2d_non_finite_stays_in_its_cone():
+    """Infinite and NaN field values spread as in the single-step kernel:
+    walls and cells outside the grid stay exact."""
+    pb = _problem((90, 120), (0, 0, 0, 0), 0, steps=9)
+    pb.source, init = None, _state((90, 120))
+    pb2 = _problem((90, 120), (8, 8, 8, 8), 1, steps=9)
+    pb2.source = None
+    init["hx"][1, 1] = np.inf
+    init["hy"][88, 118] = np.nan
+    init["ez"][45, 60] = -np.inf
+    for p in (pb, pb2):
+        one, got = _run(p, init, (2,)), _run(p, init, (3, (64, 0, 9)))
+        for f in ("ez", "hx", "hy"):
+            assert np.array_equal(np.isfinite(one[f]), np.isfinite(got[f])), f
+            m = np.isfinite(one[f])
+            assert np.array_equal(one[f][m], got[f][m]), f
+
+
+def test_wg2d_config_rules():
+    from paper_2405_00814_amd._lib import FdtdError
+    from paper_2405_00814_amd.sim import Sim
+    s = Sim.from_problem(_problem((90, 120), (8, 8, 8, 8), 0))
+    assert s.get_kernel()["tile"][0] == 64  # the default
+    for bad in ((64, 3, 8), (64, 0, 16), (64, -1, 8), (64, 0, 8, 1), (64, 0, -2)):
+        with pytest.raises(FdtdError):
+            s.set_kernel(3, bad)
+    with pytest.raises(FdtdError):
+        s.set_kernel(3, (64, 0, 8), tb=32)
+    s.close()
