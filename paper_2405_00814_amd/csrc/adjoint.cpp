@@ -139,7 +139,7 @@ extern "C" int fdtd_adjoint_grads(fdtd_sim *sim, int64_t T, int64_t n0, int64_t 
             s.kcfg = fdtd_kernel_config{};
             s.kcfg.variant = 3;
             s.kcfg.tile[0] = 64;
-            wg2d_default(s.nx, s.ny, s.mat(), s.cus, s.kcfg.tile[1], s.kcfg.tile[2]);
+            wg2d_default({{s.nx, s.ny}}, s.mat(), s.cus, s.kcfg.tile[1], s.kcfg.tile[2]);
             s.kcfg.tb = 1;
         }
         if (s.kcfg.variant != 2 && s.kcfg.variant != 3) fail(FDTD_EINVAL, "no fused 2D kernel for this grid");

@@ -5,6 +5,7 @@
 
 #include <cstdint>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "gemfdtd.h"
@@ -174,7 +175,8 @@ hipError_t launch_2d_tb(const Prob2D &p, const Prob2D *probs_dev, const Tile2T *
 // 2D, several steps per pass, one workgroup per tile of 64 columns, the
 // tile's state in registers (k2dw.hpp).  Loaded: rows from a, columns from
 // c; written: rows [i0, i1), columns [j0, j1).  kind: 0 = neither walls nor
-// slab cells nor cells outside the grid, 1 = no slab cells, 2 = any.
+// slab cells nor cells outside the grid; 1 = no slab cells, 2 = no x-slab
+// rows, 3 = no y-slab columns, 4 = any.
 struct TileW {
     int prob, kind, i0, i1, j0, j1, a, c;
 };
@@ -196,8 +198,8 @@ struct WgArgs {
     CapArgs cap;
     TapArgs tap;
 };
-// Tile rows by size class and material maps: of tiles without slab cells,
-// with x-slab rows or y-slab columns, with both.
+// Tile rows by size class and material maps: of tiles of kind 0, of kinds 1
+// to 3, of kind 4.
 struct WgShape {
     int none, one, both;
 };
@@ -214,8 +216,9 @@ bool wg2d_supported(int ny, int sx, int sy, int cls, int TB);
 // tiles of one problem for passes of at most TB steps, ordered by rows
 void wg2d_plan(int prob, int nx, int ny, int cls, int mat, int TB, const int *xlohi, const int *ylohi,
                std::vector<TileW> &tiles);
-// size class and steps per pass for a grid on `cus` compute units
-void wg2d_default(int nx, int ny, int mat, int cus, int &cls, int &TB);
+// size class and steps per pass for grids (nx, ny) advanced together on
+// `cus` compute units
+void wg2d_default(const std::vector<std::pair<int, int>> &grids, int mat, int cus, int &cls, int &TB);
 // xt: 0 plain, 1 with a.cap, 2 with a.tap (single problem only)
 hipError_t launch_2d_wg(const WgArgs &a, int cls, int mat, int xt, hipStream_t st);
 int fused2d_ntiles(int nx, int ny, const Fused2DCfg &c);

@@ -68,6 +68,18 @@ __device__ __forceinline__ int opaque(int x) {
     return x;
 }
 
+// A value at a uniform address that nothing writes while the kernel runs, by
+// scalar loads.
+template <class T>
+__device__ __forceinline__ T load_const(const T *p) {
+#ifdef __HIP_DEVICE_COMPILE__
+    typedef const T __attribute__((address_space(4))) *cptr;
+    return *(cptr)(uintptr_t)p;
+#else
+    return *p;
+#endif
+}
+
 // f(0) .. f(N - 1) with compile-time indices: the row arrays are indexed by
 // constants from the start, so they live in registers (loops unrolled by the
 // optimiser left some of them in scratch memory).
@@ -226,18 +238,19 @@ __device__ __forceinline__ void wg_tile(const Prob2D &p, const TileW &T, const W
     const int si0 = hs ? p.src_box[0] : 0, si1 = hs ? p.src_box[1] : 0, sj0 = p.src_box[2], sj1 = p.src_box[3];
     const bool srcw = hs && si0 < ib + R && si1 > ib && sj0 < T.c + 64 && sj1 > T.c;
     const bool srcj = j >= sj0 && j < sj1;
-    auto src_at = [&](int64_t n) { return srcw && n < p.src_len ? p.src_vals[n] : 0.f; };
+    auto src_at = [&](int64_t n) { return srcw && n < p.src_len ? load_const(p.src_vals + n) : 0.f; };
     float sval = src_at(step);
 
     // probes of the tile held by this wavefront: the first two cached, the
     // others looked up at every step
-    const int pbeg = A.pt.start != nullptr ? A.pt.start[tile] : 0, pend = A.pt.start != nullptr ? A.pt.start[tile + 1] : 0;
+    const int pbeg = A.pt.start != nullptr ? load_const(A.pt.start + tile) : 0,
+              pend = A.pt.start != nullptr ? load_const(A.pt.start + tile + 1) : 0;
     int np = 0, pr0 = 0, pl0 = -1, ps0 = 0, pr1 = 0, pl1 = -1, ps1 = 0, prest = pend;
     for (int q = pbeg; q < pend; ++q) {
-        const int cell = A.pt.cell[q], pi = cell / ny, pj = cell - pi * ny;
+        const int cell = load_const(A.pt.cell + q), pi = cell / ny, pj = cell - pi * ny;
         if (pi < ib || pi >= ib + R) continue;
-        if (np == 0) { pr0 = pi - ib; pl0 = pj - T.c; ps0 = A.pt.slot[q]; }
-        else if (np == 1) { pr1 = pi - ib; pl1 = pj - T.c; ps1 = A.pt.slot[q]; }
+        if (np == 0) { pr0 = pi - ib; pl0 = pj - T.c; ps0 = load_const(A.pt.slot + q); }
+        else if (np == 1) { pr1 = pi - ib; pl1 = pj - T.c; ps1 = load_const(A.pt.slot + q); }
         else if (np == 2) prest = q;
         ++np;
     }
@@ -361,8 +374,8 @@ __device__ __forceinline__ void wg_tile(const Prob2D &p, const TileW &T, const W
             record(pr0, pl0, ps0, step + s);
             if (np > 1) record(pr1, pl1, ps1, step + s);
             for (int q = prest; q < pend && np > 2; ++q) {
-                const int cell = A.pt.cell[q], pi = cell / ny, pj = cell - pi * ny;
-                if (pi >= ib && pi < ib + R) record(pi - ib, pj - T.c, A.pt.slot[q], step + s);
+                const int cell = load_const(A.pt.cell + q), pi = cell / ny, pj = cell - pi * ny;
+                if (pi >= ib && pi < ib + R) record(pi - ib, pj - T.c, load_const(A.pt.slot + q), step + s);
             }
         }
         if constexpr (XT == 2) {
@@ -422,19 +435,22 @@ __device__ __forceinline__ void wg_tile(const Prob2D &p, const TileW &T, const W
     }
 }
 
-// R, RQ, RP: rows per wavefront of the tiles without slab cells, with one
-// kind of them, with both; W wavefronts; MW: wavefronts per SIMD the
+// R, RQ, RP: rows per wavefront of the tiles of kind 0, kinds 1 to 3, kind
+// 4; W wavefronts; MW: wavefronts per SIMD the
 // registers must allow.
 template <int R, int RQ, int RP, int W, int MW, int MAT, bool BATCH, int XT>
 __global__ __launch_bounds__(64 * W, MW) void k2d_wg(WgArgs A) {
     __shared__ WgShared<W, (RQ > RP ? RQ : RP)> sh;
     const int tile = xcd_block((int)blockIdx.x, (int)gridDim.x);
     if (tile >= A.ntiles) return;  // whole workgroup
-    const TileW T = A.tiles[tile];
-    const Prob2D &p = BATCH ? A.probs[T.prob] : A.p;
-    const int64_t step = (BATCH ? *A.step_base : 0) + A.step;
+    const TileW T = load_const(A.tiles + tile);
+    // the problem by value: its pointers and sizes are scalars for the whole
+    // tile (behind a pointer they were read again after every store, into
+    // vector registers)
+    const Prob2D p = BATCH ? load_const(A.probs + T.prob) : A.p;
+    const int64_t step = (BATCH ? load_const(A.step_base) : 0) + A.step;
     if (T.kind == 0) wg_tile<R, W, MAT, false, false, false, XT>(p, T, A, step, tile, sh);
-    else if (T.kind == 1) wg_tile<R, W, MAT, true, false, false, XT>(p, T, A, step, tile, sh);
+    else if (T.kind == 1) wg_tile<RQ, W, MAT, true, false, false, XT>(p, T, A, step, tile, sh);
     else if (T.kind == 2) wg_tile<RQ, W, MAT, true, false, true, XT>(p, T, A, step, tile, sh);
     else if (T.kind == 3) wg_tile<RQ, W, MAT, true, true, false, XT>(p, T, A, step, tile, sh);
     else wg_tile<RP, W, MAT, true, true, true, XT>(p, T, A, step, tile, sh);
@@ -442,6 +458,8 @@ __global__ __launch_bounds__(64 * W, MW) void k2d_wg(WgArgs A) {
 
 template <int R, int RQ, int RP, int W, int MW, int MAT>
 static hipError_t wg_go(const WgArgs &a, int xt, hipStream_t st) {
+    // the instances that keep design values or samples need more registers
+    constexpr int MX = R > 8 ? 3 : MW;
     const dim3 g((unsigned)((a.ntiles + 7) / 8 * 8)), b(64 * W);
     if (a.probs) {
         if (xt != 0) return hipErrorInvalidValue;
@@ -449,9 +467,9 @@ static hipError_t wg_go(const WgArgs &a, int xt, hipStream_t st) {
     } else if (xt == 0) {
         hipLaunchKernelGGL((k2d_wg<R, RQ, RP, W, MW, MAT, false, 0>), g, b, 0, st, a);
     } else if (xt == 1) {
-        hipLaunchKernelGGL((k2d_wg<R, RQ, RP, W, MW, MAT, false, 1>), g, b, 0, st, a);
+        hipLaunchKernelGGL((k2d_wg<R, RQ, RP, W, MX, MAT, false, 1>), g, b, 0, st, a);
     } else {
-        hipLaunchKernelGGL((k2d_wg<R, RQ, RP, W, MW, MAT, false, 2>), g, b, 0, st, a);
+        hipLaunchKernelGGL((k2d_wg<R, RQ, RP, W, MX, MAT, false, 2>), g, b, 0, st, a);
     }
     return hipGetLastError();
 }

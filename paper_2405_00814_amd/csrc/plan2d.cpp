@@ -84,9 +84,13 @@ bool res2d_supported(int nx, int ny, bool cpml, int np) {
 // launches: 14 while all tiles run at once, 12, or 10 where 12 would start
 // another round (1024^2: 10 steps 2.42, 12 steps 2.79; 4096^2: 12 steps
 // 14.3, 8 steps 18.0; with a Db map, 64-row tiles, 10 steps 20.1, 12 20.8).
-void wg2d_default(int nx, int ny, int mat, int cus, int &cls, int &TB) {
+void wg2d_default(const std::vector<std::pair<int, int>> &grids, int mat, int cus, int &cls, int &TB) {
     auto along = [](int n, int h, int tb) { return n <= h ? 1 : 2 + std::max(0, (n - 2 * (h - tb) + h - 2 * tb - 1) / (h - 2 * tb)); };
-    auto count = [&](int h, int tb) { return (int64_t)along(nx, h, tb) * along(ny, 64, tb); };
+    auto count = [&](int h, int tb) {
+        int64_t n = 0;
+        for (const auto &g : grids) n += (int64_t)along(g.first, h, tb) * along(g.second, 64, tb);
+        return n;
+    };
     if (count(32, 12) <= 2 * (int64_t)cus) {
         cls = 0;
         TB = count(32, 14) <= cus ? 14 : 12;
@@ -114,28 +118,31 @@ void wg2d_plan(int prob, int nx, int ny, int cls, int mat, int TB, const int *xl
         const bool ey = c == 0 || c + 64 > ny;
         for (int i0 = 0; i0 < nx;) {
             int a = i0 > 0 ? i0 - TB : 0;
-            // kind and height of a tile loading rows from a
-            auto slab = [&](int rows) { return (xlo > 0 && a - 1 < xlo) || (xhi > 0 && a + rows > nx - xhi); };
-            int kind, rows = py ? sh.one : sh.none;
-            if (!slab(rows)) {
-                kind = py ? 2 : (ey || a == 0 || a + rows > nx ? 1 : 0);
+            auto slab = [&](int rows) { return (xlo > 0 && a < xlo) || (xhi > 0 && a + rows > nx - xhi); };
+            // the tallest tile that the rows from a allow: clear of the x
+            // slabs, and (kind 0) of the walls and the grid's end
+            const int tall = py ? sh.one : sh.none;
+            const bool edge = ey || a == 0;
+            int kind, rows;
+            if (!slab(tall) && (py || (!edge && a + tall <= nx))) {
+                kind = py ? 2 : 0;
+                rows = tall;
             } else {
-                // a tile that would reach into the last slab is moved up to
-                // end before it, where that leaves it at least half its rows
-                const int a2 = nx - xhi - rows;
-                if (xhi > 0 && a2 < a && a2 >= 1 && a2 - 1 >= xlo && a2 + rows - TB - i0 >= (rows - 2 * TB) / 2) {
+                // a tile that would reach into the last slab (or past the
+                // last row) is moved up to end before it, where that leaves
+                // it at least half its rows
+                const int a2 = nx - xhi - tall;
+                if (a2 < a && a2 >= std::max(xlo, 1) && (py ? xhi > 0 : !ey) &&
+                    a2 + tall - (xhi > 0 ? TB : 0) - i0 >= (tall - 2 * TB) / 2) {
                     a = a2;
-                    kind = py ? 2 : (ey ? 1 : 0);
+                    kind = py ? 2 : 0;
+                    rows = tall;
+                } else if (!slab(sh.one)) {
+                    kind = py ? 2 : 1;
+                    rows = sh.one;
                 } else {
-                    rows = py ? sh.both : sh.one;
                     kind = py ? 4 : 3;
-                    // (with the smaller height the slab may be out of reach)
-                    if (!slab(rows)) kind = py ? 2 : (ey || a == 0 || a + rows > nx ? 1 : 0);
-                    if (kind < 3) rows = py ? sh.one : sh.none;
-                    if (kind < 3 && slab(rows)) {
-                        rows = py ? sh.both : sh.one;
-                        kind = py ? 4 : 3;
-                    }
+                    rows = py ? sh.both : sh.one;
                 }
             }
             const int i1 = a + rows >= nx ? nx : a + rows - TB;

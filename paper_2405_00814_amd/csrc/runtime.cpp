@@ -483,7 +483,7 @@ void Sim::build_probe_tiles() {
         const int xl[2] = {ax[0].lo, ax[0].hi}, yl[2] = {ax[1].lo, ax[1].hi};
         std::vector<TileW> tl;
         if (kcfg.variant == 4) {
-            wg2d_default(nx, ny, mat, cus, wg_cls, wg_tb);
+            wg2d_default({{nx, ny}}, mat, cus, wg_cls, wg_tb);
         } else {
             wg_cls = kcfg.tile[1];
             wg_tb = kcfg.tile[2];
@@ -971,7 +971,7 @@ int default_variant_tiles(const Sim &s, fdtd_kernel_config &k) {
             return 0;
         }
         int cls, wtb;
-        wg2d_default(s.nx, s.ny, s.mat(), s.cus, cls, wtb);
+        wg2d_default({{s.nx, s.ny}}, s.mat(), s.cus, cls, wtb);
         const bool strip = s.nx < 40 && s.ncell >= kTB2MinCells;  // a tile's rows would lie mostly outside
         if (!strip && wg2d_supported(s.ny, s.ax[0].lo + s.ax[0].hi, s.ax[1].lo + s.ax[1].hi, cls, wtb)) {
             k.variant = 3;

@@ -34,7 +34,7 @@ int main() {
         for (const TileW &T : t) {
             if (T.kind < 0 || T.kind > 4 || T.prob != 7) { ok = false; break; }
             kinds[T.kind]++;
-            const int rows = T.kind < 2 ? sh.none : T.kind < 4 ? sh.one : sh.both;
+            const int rows = T.kind == 0 ? sh.none : T.kind < 4 ? sh.one : sh.both;
             ok = ok && T.a >= 0 && T.a < nx && T.c >= 0 && T.c < ny && T.i0 < T.i1 && T.j0 < T.j1;
             ok = ok && T.i0 >= T.a && T.i1 <= T.a + rows && T.i1 <= nx && T.j0 >= T.c && T.j1 <= T.c + 64 && T.j1 <= ny;
             ok = ok && (T.a == 0 || T.i0 - T.a >= TB) && (T.a + rows >= nx || T.a + rows - T.i1 >= TB);

@@ -125,3 +125,29 @@ def test_wg2d_config_rules():
     with pytest.raises(FdtdError):
         s.set_kernel(3, (64, 0, 8), tb=32)
     s.close()
+
+
+def test_wg2d_batch_bits():
+    """Enough cells for the batch's largest tiles, sources near the corners
+    of the absorbing layer, one problem with loss: the bits of the
+    single-problem single-step kernel."""
+    from paper_2405_00814_amd.sim import Batch, Sim
+    probs = []
+    for q, (nx, ny, cell) in enumerate([(820, 831, (18, 18)), (843, 820, (822, 799)), (273, 259, (20, 238)),
+                                        (80, 97, (40, 40))]):
+        pb = W.dielectric2d(nx, ny=ny, steps=80, seed=q, nrect=20, side=(8, 60), npml=16, nprobes=3, lossy=q == 1)
+        pb.source.cell = cell
+        pb.probes = np.array([cell, (cell[0], cell[1] + 3)], np.int32)
+        probs.append(pb)
+    b = Batch(probs)
+    for n in (1, 50, 29):
+        b.step(n)
+    for q, pb in enumerate(probs):
+        s = Sim.from_problem(pb)
+        s.set_kernel(2)
+        s.step(80)
+        for f in ("ez", "hx", "hy"):
+            assert np.array_equal(b.get_field(q, f), s.get_field(f)), (q, f)
+        assert np.array_equal(b.probe(q), s.probe()), q
+        s.close()
+    b.close()
