@@ -316,6 +316,45 @@ extern "C" int fdtd_adjoint_grads(fdtd_sim *sim, int64_t T, int64_t n0, int64_t 
         hip_check(hipMemcpyAsync(d_tcell, tcell.data(), tcell.size() * 4, hipMemcpyHostToDevice, s.st), "upload");
         hip_check(hipMemcpyAsync(d_tslot, tslot.data(), tslot.size() * 4, hipMemcpyHostToDevice, s.st), "upload");
         const ProbeTiles apt{d_tst, d_tcell, d_tslot};
+        // several adjoint steps per pass in workgroup tiles (size class 0 or
+        // 1: with the design cells' sums in registers as well, 8 rows per
+        // wavefront are the most), each tile seeding the probes of all the
+        // cells it loads
+        int acls = 0, atb = 0;
+        wg2d_default({{s.nx, s.ny}}, s.mat(), s.cus, acls, atb);
+        if (acls == 2) {
+            acls = 1;
+            atb = 10;
+        }
+        const bool awg = wg2d_supported(s.ny, s.ax[0].lo + s.ax[0].hi, s.ax[1].lo + s.ax[1].hi, acls, atb);
+        std::vector<TileW> wtl;
+        std::vector<int> wst, wcell, wslot;
+        TileW *d_wtl = nullptr;
+        ProbeTiles wpt{};
+        if (awg) {
+            const int xl[2] = {s.ax[0].lo, s.ax[0].hi}, yl[2] = {s.ax[1].lo, s.ax[1].hi};
+            wg2d_plan(0, s.nx, s.ny, acls, s.mat(), atb, xl, yl, wtl);
+            const int rows = wg2d_shape(acls, s.mat()).none;  // of every kind in these classes
+            wst.push_back(0);
+            for (const TileW &t : wtl) {
+                for (size_t q = 0; q < pcell.size(); ++q) {
+                    const int i = pcell[q] / s.ny, j = pcell[q] % s.ny;
+                    if (i < t.a || i >= t.a + rows || j < t.c || j >= t.c + 64) continue;
+                    wcell.push_back(pcell[q]);
+                    wslot.push_back(pslot[q]);
+                }
+                wst.push_back((int)wcell.size());
+            }
+            auto up = [&](const void *h, size_t n, size_t bytes) {
+                void *d = get(std::max<size_t>(1, n) * bytes);
+                if (n) hip_check(hipMemcpyAsync(d, h, n * bytes, hipMemcpyHostToDevice, s.st), "upload");
+                return d;
+            };
+            d_wtl = (TileW *)up(wtl.data(), wtl.size(), sizeof(TileW));
+            wpt.start = (int *)up(wst.data(), wst.size(), 4);
+            wpt.cell = (int *)up(wcell.data(), wcell.size(), 4);
+            wpt.slot = (int *)up(wslot.data(), wslot.size(), 4);
+        }
         hip_check(hipStreamSynchronize(s.st), "sync");
         // ---- backward over segments, newest first (the last one kept by
         //      the forward).  Segment g's adjoint steps run on the
@@ -357,7 +396,42 @@ extern "C" int fdtd_adjoint_grads(fdtd_sim *sim, int64_t T, int64_t n0, int64_t 
             if (g >= 1) recompute(g - 1);
             if (g + 1 < nseg) hip_check(hipStreamWaitEvent(st0, ev_rec[b], 0), "stream wait");
             const Prob2D p = s.prob2d(0, 0);
-            for (int64_t k = k1 - 1; k >= k0; --k) {
+            for (int64_t k = k1 - 1; awg && k >= k0;) {
+                // the first step's input is seeded here, every later one by
+                // the pass that writes it
+                if (k == T - 1 && T > n0 && T <= n1)
+                    hip_check(launch_adj2d_seed(a[acur].ez, d_ust, d_pcell, d_pslot, nu, rec_snap, s.rec_cap, T - 1,
+                                                st0),
+                              "adjoint seed");
+                const int64_t left = k - k0 + 1, most = wtl.size() == 1 ? left : atb, np = (left + most - 1) / most;
+                AdjWArgs w{};
+                w.p = p;
+                w.l0 = a[acur];
+                w.l1 = a[1 - acur];
+                w.tiles = d_wtl;
+                w.ntiles = (int)wtl.size();
+                w.nsteps = (int)((left + np - 1) / np);
+                w.k = k;
+                w.k0 = k0;
+                w.nd = ndc;
+                w.n0 = n0;
+                w.n1 = n1;
+                w.design = make_int4(i0, i1, j0, j1);
+                w.cbox = make_int4(cbox[0], cbox[1], cbox[2], cbox[3]);
+                w.cap_ez = cap_ez[b];
+                w.cap_br = cap_br[b];
+                w.sez = sez;
+                w.sbr = sbr;
+                w.shx = shx;
+                w.shy = shy;
+                w.pt = wpt;
+                w.rec = rec_snap;
+                w.rec_stride = s.rec_cap;
+                hip_check(launch_adj2d_wg(w, acls, s.mat(), st0), "adjoint steps");
+                acur = 1 - acur;
+                k -= w.nsteps;
+            }
+            for (int64_t k = k1 - 1; !awg && k >= k0; --k) {
                 // the first step's input is seeded here, every later one by
                 // the step that writes it
                 if (k == T - 1 && T > n0 && T <= n1)

@@ -397,6 +397,26 @@ hipError_t launch_adj2d_fused(const Prob2D &p, const Adj2D &l0, const Adj2D &l1,
                               const int *cbox, const float *cap_ez, const float *cap_br, double *sez, double *sbr,
                               double *shx, double *shy, int seed_out, const ProbeTiles &pt, const float *rec,
                               int64_t rec_stride, int64_t seed_k, int V, int TX, hipStream_t st);
+// Adjoint steps k, k - 1, .. k - nsteps + 1 in one pass of workgroup tiles
+// (kadjw.hpp; the tiles of wg2d_plan with size class 0 or 1): reads l0,
+// writes l1.  design, cbox, cap_ez, cap_br, sez .. shy as below, cap_* of
+// step q at (q - k0) * nd.  pt: probes grouped by the tiles whose loaded
+// cells hold them; the seed 2 rec[slot][q - 1] is added after step q where
+// n0 < q <= n1.
+struct AdjWArgs {
+    Prob2D p;
+    Adj2D l0, l1;
+    const TileW *tiles;
+    int ntiles, nsteps;
+    int64_t k, k0, nd, n0, n1;
+    int4 design, cbox;
+    const float *cap_ez, *cap_br;
+    double *sez, *sbr, *shx, *shy;
+    ProbeTiles pt;
+    const float *rec;
+    int64_t rec_stride;
+};
+hipError_t launch_adj2d_wg(const AdjWArgs &a, int cls, int mat, hipStream_t st);
 // The seed of the first adjoint step: ez[cell u] += 2 * rec[slot][k] over
 // the probe entries [start[u], start[u+1]) of the nu probed cells.
 hipError_t launch_adj2d_seed(float *ez, const int *seed_start, const int *seed_cell, const int *seed_slot, int nu,

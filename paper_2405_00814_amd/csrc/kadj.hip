@@ -16,7 +16,8 @@
 namespace gem {
 
 // ---------------------------------------------------------------------------
-// Fused adjoint step: the three phases above in one pass over memory, by the
+// Fused adjoint step (for grids whose rows are too long for the workgroup
+// tiles of kadjw.hpp): the three phases above in one pass over memory, by the
 // forward kernel's tiling (a wavefront marches TX rows of a 64*V column
 // strip).  Double buffered: the adjoint state of step k+1 is read from L0,
 // that of step k written to L1.  At row i the wavefront has phase A of rows i
