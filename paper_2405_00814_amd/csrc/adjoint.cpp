@@ -139,7 +139,7 @@ extern "C" int fdtd_adjoint_grads(fdtd_sim *sim, int64_t T, int64_t n0, int64_t 
             s.kcfg = fdtd_kernel_config{};
             s.kcfg.variant = 3;
             s.kcfg.tile[0] = 64;
-            wg2d_default({{s.nx, s.ny}}, s.mat(), s.cus, s.kcfg.tile[1], s.kcfg.tile[2]);
+            wg2d_default({{s.nx, s.ny}}, s.wmat(), s.cus, s.kcfg.tile[1], s.kcfg.tile[2]);
             s.kcfg.tb = 1;
         }
         if (s.kcfg.variant != 2 && s.kcfg.variant != 3) fail(FDTD_EINVAL, "no fused 2D kernel for this grid");
@@ -321,7 +321,7 @@ extern "C" int fdtd_adjoint_grads(fdtd_sim *sim, int64_t T, int64_t n0, int64_t 
         // wavefront are the most), each tile seeding the probes of all the
         // cells it loads
         int acls = 0, atb = 0;
-        wg2d_default({{s.nx, s.ny}}, s.mat(), s.cus, acls, atb);
+        wg2d_default({{s.nx, s.ny}}, s.wmat(), s.cus, acls, atb);
         if (acls == 2) {
             acls = 1;
             atb = 10;
@@ -333,8 +333,8 @@ extern "C" int fdtd_adjoint_grads(fdtd_sim *sim, int64_t T, int64_t n0, int64_t 
         ProbeTiles wpt{};
         if (awg) {
             const int xl[2] = {s.ax[0].lo, s.ax[0].hi}, yl[2] = {s.ax[1].lo, s.ax[1].hi};
-            wg2d_plan(0, s.nx, s.ny, acls, s.mat(), atb, xl, yl, wtl);
-            const int rows = wg2d_shape(acls, s.mat()).none;  // of every kind in these classes
+            wg2d_plan(0, s.nx, s.ny, acls, s.wmat(), atb, xl, yl, wtl);
+            const int rows = wg2d_shape(acls, s.wmat()).none;  // of every kind in these classes
             wst.push_back(0);
             for (const TileW &t : wtl) {
                 for (size_t q = 0; q < pcell.size(); ++q) {

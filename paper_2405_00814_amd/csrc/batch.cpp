@@ -281,10 +281,13 @@ static void batch_build_tb(fdtd_batch &b) {
     if (b.tb == 4 && b.tb_tx == 16 && b.tb_vmax == 1 && b.tb_txo == 0) {
         WgGroup w;
         std::vector<std::pair<int, int>> grids;
+        bool ca = false, db = false;
         for (const Sim *s : b.sims) {
             grids.push_back({s->nx, s->ny});
-            w.mat = std::max(w.mat, s->mat());
+            ca = ca || s->lossy;
+            db = db || s->mumap;
         }
+        w.mat = db ? (ca ? 2 : 3) : (ca ? 1 : 0);
         wg2d_default(grids, w.mat, b.sims[0]->cus, w.cls, w.TB);
         bool ok = true;
         for (const Sim *s : b.sims)

@@ -198,7 +198,8 @@ struct WgArgs {
     CapArgs cap;
     TapArgs tap;
 };
-// Tile rows by size class and material maps: of tiles of kind 0, of kinds 1
+// Tile rows by size class and maps besides Cb (mat 0: none, 1: Ca, 2: Ca and
+// Db, 3: Db): of tiles of kind 0, of kinds 1
 // to 3, of kind 4.
 struct WgShape {
     int none, one, both;
@@ -208,8 +209,8 @@ constexpr WgShape wg2d_shape(int cls, int mat) {
     return cls == 0 ? WgShape{32, 32, 32}
          : cls == 1 ? WgShape{64, 64, 64}
          : mat == 0 ? WgShape{96, 56, 40}
-         : mat == 1 ? WgShape{80, 48, 36}
-                    : WgShape{64, 40, 32};
+         : mat == 2 ? WgShape{64, 40, 32}
+                    : WgShape{80, 48, 36};
 }
 // (sx, sy: rows and columns of the x and y slabs)
 bool wg2d_supported(int ny, int sx, int sy, int cls, int TB);

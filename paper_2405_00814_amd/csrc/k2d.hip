@@ -306,7 +306,7 @@ __device__ __forceinline__ void fused2d_tile(const Prob2D &p, int TX, int cx, in
             if (i >= 1 && j >= 1) {
                 const float dHy = hy_n[v] - hy_p[v];
                 const float dHx = hx_n[v] - hx_l[v];
-                float br = __builtin_fmaf(-kEy[v], dHx, kEx * dHy);
+                float br = __builtin_fmaf(kEx, dHy, -(kEy[v] * dHx));
                 if (PML && ii >= 0) {
                     pex_n[v] = __builtin_fmaf(p.x.cE[i], dHy, p.x.bE[i] * pex_o[v]);
                     br += pex_n[v];

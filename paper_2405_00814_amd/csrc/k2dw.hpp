@@ -116,6 +116,7 @@ struct WgShared {
     RowTab x[W * RP + 1];        // x-axis tables (CPML tiles); entry 0: row a - 1
 };
 
+// MAT: 0 = Cb map; 1 = Ca, 2 = Ca and Db, 3 = Db map besides it.
 // EDGE: the tile holds wall cells (row 0, column 0) or cells outside the
 // grid; PX, PY: it holds x-slab rows, y-slab columns (imply EDGE).  XT: 0 = none, 1 = the
 // design cells' values are kept (adjoint), 2 = monitor samples are kept.
@@ -123,6 +124,7 @@ template <int R, int W, int MAT, bool EDGE, bool PX, bool PY, int XT, class SH>
 __device__ __forceinline__ void wg_tile(const Prob2D &p, const TileW &T, const WgArgs &A, int64_t step, int tile,
                                         SH &sh) {
 #pragma clang fp contract(off)
+    constexpr bool CA = MAT == 1 || MAT == 2, DB = MAT >= 2;
     const int lane = (int)(threadIdx.x & 63);
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int nx = p.nx, ny = p.ny;
@@ -158,19 +160,19 @@ __device__ __forceinline__ void wg_tile(const Prob2D &p, const TileW &T, const W
                 t.h = make_float4(p.x.kH[i], in ? p.x.bH[i] : 0.f, in ? p.x.cH[i] : 0.f, 0.f);
                 t.e = make_float4(p.x.kE[i], in ? p.x.bE[i] : 0.f, in ? p.x.cE[i] : 0.f, 0.f);
             }
-            if (MAT < 2) t.h.x *= db0;
+            if (!DB) t.h.x *= db0;
             sh.x[q] = t;
         }
     }
 
     float ez[R], hx[R], hy[R], cb[R];
-    float ca[MAT >= 1 ? R : 1], db[MAT == 2 ? R : 1];
+    float ca[CA ? R : 1], db[DB ? R : 1];
     float phx[PY ? R : 1], pzy[PY ? R : 1], phy[PX ? R : 1], pzx[PX ? R : 1];
     const int64_t first = (int64_t)T.a * ny, len = (int64_t)nx * ny;
     const int rb = ny * 4, vo = jc * 4;  // bytes per row, the lane's column
     {
         const Buf bez(p.s0.ez, first, len), bhx(p.s0.hx, first, len), bhy(p.s0.hy, first, len), bcb(p.cb, first, len);
-        const Buf bca(MAT >= 1 && p.ca ? p.ca : p.cb, first, len), bdb(MAT == 2 && p.db ? p.db : p.cb, first, len);
+        const Buf bca(CA ? p.ca : p.cb, first, len), bdb(DB ? p.db : p.cb, first, len);
         rows<R>([&](auto rc) GEM_INL {
             constexpr int r = decltype(rc)::value;
             const int i = ib + r;
@@ -183,14 +185,11 @@ __device__ __forceinline__ void wg_tile(const Prob2D &p, const TileW &T, const W
             hy[r] = in ? y : 0.f;
             // Cb > 0 in every cell the E layer updates; 0 marks the others
             cb[r] = in && colup && (!EDGE || i >= 1) ? b : 0.f;
-            if constexpr (MAT >= 1) {
-                ca[r] = 1.f;
-                if (p.ca) { const float c = bca.ld(vo, so); ca[r] = in ? c : 1.f; }
+            if constexpr (CA) {
+                const float c = bca.ld(vo, so);
+                ca[r] = in ? c : 1.f;
             }
-            if constexpr (MAT == 2) {
-                db[r] = db0;
-                if (p.db) db[r] = bdb.ld(vo, so);
-            }
+            if constexpr (DB) db[r] = bdb.ld(vo, so);
         });
     }
     if constexpr (PY) {
@@ -226,7 +225,7 @@ __device__ __forceinline__ void wg_tile(const Prob2D &p, const TileW &T, const W
         const int64_t row = (int64_t)(ib - 1) * ny;
         const float y = (p.s0.hy + row)[jc];
         hyp = colin ? y : 0.f;
-        if (MAT == 2 && p.db) dbp = (p.db + row)[jc];
+        if constexpr (DB) dbp = (p.db + row)[jc];
         if constexpr (PX) {
             const int ii = slab_index(p.x, ib - 1);
             if (ii >= 0 && colin) php = (p.s0.psi_hy + (int64_t)ii * ny)[jc];
@@ -289,10 +288,10 @@ __device__ __forceinline__ void wg_tile(const Prob2D &p, const TileW &T, const W
         // ---- H layer ----
         {
             const float d = ez[0] - up;
-            float k = MAT == 2 ? kHx0 : wHx0, b = 0.f, c = 0.f;
+            float k = DB ? kHx0 : wHx0, b = 0.f, c = 0.f;
             if constexpr (PX) { const float4 t = sh.x[w * R].h; k = t.x; b = t.y; c = t.z; }
             if constexpr (PX) php = __builtin_fmaf(c, d, b * php);
-            if constexpr (MAT == 2) {
+            if constexpr (DB) {
                 float t = d * k;
                 if constexpr (PX) t += php;
                 hyp = __builtin_fmaf(dbp, t, hyp);
@@ -306,11 +305,11 @@ __device__ __forceinline__ void wg_tile(const Prob2D &p, const TileW &T, const W
             const float e = ez[r];
             const float dy = lane_next0(e) - e;
             const float dx = (r + 1 < R ? ez[r + 1 < R ? r + 1 : r] : dn) - e;
-            float k = MAT == 2 ? kHx0 : wHx0, b = 0.f, c = 0.f;
+            float k = DB ? kHx0 : wHx0, b = 0.f, c = 0.f;
             if constexpr (PX) { const float4 t = sh.x[w * R + r + 1].h; k = t.x; b = t.y; c = t.z; }
             if constexpr (PY) phx[r] = __builtin_fmaf(cHy, dy, bHy * phx[r]);
             if constexpr (PX) phy[r] = __builtin_fmaf(c, dx, b * phy[r]);
-            if constexpr (MAT == 2) {
+            if constexpr (DB) {
                 float ty = dy * kHy, tx = dx * k;
                 if constexpr (PY) ty += phx[r];
                 if constexpr (PX) tx += phy[r];
@@ -333,7 +332,7 @@ __device__ __forceinline__ void wg_tile(const Prob2D &p, const TileW &T, const W
             const bool upd = !EDGE || cb[r] != 0.f;
             float k = kEx0, b = 0.f, c = 0.f;
             if constexpr (PX) { const float4 t = sh.x[w * R + r + 1].e; k = t.x; b = t.y; c = t.z; }
-            float t = __builtin_fmaf(-kEy, dx, k * dy);
+            float t = __builtin_fmaf(k, dy, -(kEy * dx));
             if constexpr (PX) {
                 const float q = __builtin_fmaf(c, dy, b * pzx[r]);
                 pzx[r] = upd ? q : pzx[r];
@@ -354,7 +353,9 @@ __device__ __forceinline__ void wg_tile(const Prob2D &p, const TileW &T, const W
                 }
             }
             float n;
-            if constexpr (MAT >= 1) n = __builtin_fmaf(cb[r], t, ca[r] * ez[r]);
+            // (fma(ca, ez, cb t) needed more registers than there are: 4096^2
+            // 22 us per step for 16)
+            if constexpr (CA) n = __builtin_fmaf(cb[r], t, ca[r] * ez[r]);
             else n = __builtin_fmaf(cb[r], t, ez[r]);
             ez[r] = upd ? n : ez[r];
             if (r % 4 == 3) __builtin_amdgcn_sched_barrier(0);
@@ -438,6 +439,16 @@ __device__ __forceinline__ void wg_tile(const Prob2D &p, const TileW &T, const W
 // R, RQ, RP: rows per wavefront of the tiles of kind 0, kinds 1 to 3, kind
 // 4; W wavefronts; MW: wavefronts per SIMD the
 // registers must allow.
+template <int R, int RQ, int RP, int W, int MAT, int XT, class SH>
+__device__ __forceinline__ void wg_kind(const Prob2D &p, const TileW &T, const WgArgs &A, int64_t step, int tile,
+                                        SH &sh) {
+    if (T.kind == 0) wg_tile<R, W, MAT, false, false, false, XT>(p, T, A, step, tile, sh);
+    else if (T.kind == 1) wg_tile<RQ, W, MAT, true, false, false, XT>(p, T, A, step, tile, sh);
+    else if (T.kind == 2) wg_tile<RQ, W, MAT, true, false, true, XT>(p, T, A, step, tile, sh);
+    else if (T.kind == 3) wg_tile<RQ, W, MAT, true, true, false, XT>(p, T, A, step, tile, sh);
+    else wg_tile<RP, W, MAT, true, true, true, XT>(p, T, A, step, tile, sh);
+}
+
 template <int R, int RQ, int RP, int W, int MW, int MAT, bool BATCH, int XT>
 __global__ __launch_bounds__(64 * W, MW) void k2d_wg(WgArgs A) {
     __shared__ WgShared<W, (RQ > RP ? RQ : RP)> sh;
@@ -449,11 +460,21 @@ __global__ __launch_bounds__(64 * W, MW) void k2d_wg(WgArgs A) {
     // vector registers)
     const Prob2D p = BATCH ? load_const(A.probs + T.prob) : A.p;
     const int64_t step = (BATCH ? load_const(A.step_base) : 0) + A.step;
-    if (T.kind == 0) wg_tile<R, W, MAT, false, false, false, XT>(p, T, A, step, tile, sh);
-    else if (T.kind == 1) wg_tile<RQ, W, MAT, true, false, false, XT>(p, T, A, step, tile, sh);
-    else if (T.kind == 2) wg_tile<RQ, W, MAT, true, false, true, XT>(p, T, A, step, tile, sh);
-    else if (T.kind == 3) wg_tile<RQ, W, MAT, true, true, false, XT>(p, T, A, step, tile, sh);
-    else wg_tile<RP, W, MAT, true, true, true, XT>(p, T, A, step, tile, sh);
+    // a batch's problem runs the code of its own maps (MAT stands for all the
+    // maps that any of them has, and for the tiles' rows)
+    constexpr bool CA = MAT == 1 || MAT == 2, DB = MAT >= 2;
+    if constexpr (!BATCH || MAT == 0) {
+        wg_kind<R, RQ, RP, W, MAT, XT>(p, T, A, step, tile, sh);
+    } else {
+        const bool ca = CA && p.ca != nullptr, db = DB && p.db != nullptr;
+        if (!ca && !db) wg_kind<R, RQ, RP, W, 0, XT>(p, T, A, step, tile, sh);
+        if constexpr (CA)
+            if (ca && !db) wg_kind<R, RQ, RP, W, 1, XT>(p, T, A, step, tile, sh);
+        if constexpr (CA && DB)
+            if (ca && db) wg_kind<R, RQ, RP, W, 2, XT>(p, T, A, step, tile, sh);
+        if constexpr (DB)
+            if (!ca && db) wg_kind<R, RQ, RP, W, 3, XT>(p, T, A, step, tile, sh);
+    }
 }
 
 template <int R, int RQ, int RP, int W, int MW, int MAT>

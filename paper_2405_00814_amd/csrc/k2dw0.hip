@@ -6,7 +6,8 @@ namespace gem {
 hipError_t launch_2d_wg0(const WgArgs &a, int mat, int xt, hipStream_t st) {
     if (mat == 0) return wg_go<4, 4, 4, 8, 4, 0>(a, xt, st);
     if (mat == 1) return wg_go<4, 4, 4, 8, 4, 1>(a, xt, st);
-    return wg_go<4, 4, 4, 8, 4, 2>(a, xt, st);
+    if (mat == 2) return wg_go<4, 4, 4, 8, 4, 2>(a, xt, st);
+    return wg_go<4, 4, 4, 8, 4, 3>(a, xt, st);
 }
 
 }  // namespace gem

@@ -8,7 +8,8 @@ namespace gem {
 hipError_t launch_2d_wg2(const WgArgs &a, int mat, int xt, hipStream_t st) {
     if (mat == 0) return wg_go<24, 14, 10, 4, 4, 0>(a, xt, st);
     if (mat == 1) return wg_go<20, 12, 9, 4, 4, 1>(a, xt, st);
-    return wg_go<16, 10, 8, 4, 4, 2>(a, xt, st);
+    if (mat == 2) return wg_go<16, 10, 8, 4, 4, 2>(a, xt, st);
+    return wg_go<20, 12, 9, 4, 4, 3>(a, xt, st);
 }
 
 }  // namespace gem

@@ -350,7 +350,7 @@ void Sim::build_probe_tiles() {
     if (kcfg.variant < 2 || is_graph) return;
     const int a = kcfg.tile[0], b = kcfg.tile[1], c3 = kcfg.tile[2];
     const int mat = this->mat();
-    const int vm = kcfg.variant * 4 + mat;
+    const int vm = kcfg.variant * 4 + (ndim == 2 ? wmat() : mat);
     if (pt_ntiles >= 0 && pt_cfg[0] == a && pt_cfg[1] == b && pt_cfg[2] == (int)probe_cells.size() &&
         pt_cfg[3] == c3 && pt_cfg[4] == vm && pt_cfg[5] == kcfg.tile[3] && pt_start)
         return;
@@ -483,12 +483,13 @@ void Sim::build_probe_tiles() {
         const int xl[2] = {ax[0].lo, ax[0].hi}, yl[2] = {ax[1].lo, ax[1].hi};
         std::vector<TileW> tl;
         if (kcfg.variant == 4) {
-            wg2d_default({{nx, ny}}, mat, cus, wg_cls, wg_tb);
+            wg2d_default({{nx, ny}}, wmat(), cus, wg_cls, wg_tb);
         } else {
             wg_cls = kcfg.tile[1];
             wg_tb = kcfg.tile[2];
         }
-        wg2d_plan(0, nx, ny, wg_cls, mat, wg_tb, xl, yl, tl);
+        wg_mat = wmat();
+        wg2d_plan(0, nx, ny, wg_cls, wg_mat, wg_tb, xl, yl, tl);
         wg_n = (int)tl.size();
         swap_in(wg_dev, dev_upload(al, tl.data(), tl.size(), st));
         std::vector<std::pair<int, int>> ent;  // (owning tile, probe)
@@ -592,7 +593,8 @@ void Sim::launch_wg2d(int64_t step, int nsteps, const CapArgs *cap, const TapArg
     a.step = step;
     if (cap) a.cap = *cap;
     if (tap) a.tap = *tap;
-    hip_check(launch_2d_wg(a, wg_cls, mat(), cap ? 1 : (tap ? 2 : 0), st), "2d workgroup tiles");
+    if (wg_mat != wmat()) fail(FDTD_ESTATE, "tile plan out of date");
+    hip_check(launch_2d_wg(a, wg_cls, wg_mat, cap ? 1 : (tap ? 2 : 0), st), "2d workgroup tiles");
     cur = 1 - cur;
     last_launches += 1;
 }
@@ -971,7 +973,7 @@ int default_variant_tiles(const Sim &s, fdtd_kernel_config &k) {
             return 0;
         }
         int cls, wtb;
-        wg2d_default({{s.nx, s.ny}}, s.mat(), s.cus, cls, wtb);
+        wg2d_default({{s.nx, s.ny}}, s.wmat(), s.cus, cls, wtb);
         const bool strip = s.nx < 40 && s.ncell >= kTB2MinCells;  // a tile's rows would lie mostly outside
         if (!strip && wg2d_supported(s.ny, s.ax[0].lo + s.ax[0].hi, s.ax[1].lo + s.ax[1].hi, cls, wtb)) {
             k.variant = 3;

@@ -130,7 +130,7 @@ struct Sim {
     // tile[1] = size class, tile[2] = most steps per pass; variant 4): the
     // tile list and its probe groups (pt2_*)
     TileW *wg_dev = nullptr;
-    int wg_n = 0, wg_cls = 0, wg_tb = 1;
+    int wg_n = 0, wg_cls = 0, wg_tb = 1, wg_mat = -1;
     bool wg2d() const {
         return ndim == 2 && !is_graph && ((kcfg.variant == 3 && kcfg.tile[0] == 64) || (kcfg.variant == 4 && res2d_ok()));
     }
@@ -146,6 +146,8 @@ struct Sim {
     // 3D fused: launch plan and its tile lists on the device
     Wave3DPlan plan3;
     Tile3 *tl_dev = nullptr;
+    // the maps as the workgroup tiles count them (3: Db without Ca)
+    int wmat() const { return mumap && !lossy ? 3 : mat(); }
     // 3D two steps per pass (variant 3): its plan and tile lists
     TwoPlan plan2;
     TileTB *tb_dev = nullptr, *tbo_dev = nullptr;

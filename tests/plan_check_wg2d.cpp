@@ -24,7 +24,7 @@ int main() {
             for (int *v : {&xl[0], &xl[1], &yl[0], &yl[1]}) *v = U(0, 20);
         if (xl[0] + xl[1] >= nx) xl[0] = xl[1] = 0;
         if (yl[0] + yl[1] >= ny) yl[0] = yl[1] = 0;
-        const int cls = U(0, kWgClasses - 1), mat = U(0, 2), TB = U(1, 15);
+        const int cls = U(0, kWgClasses - 1), mat = U(0, 3), TB = U(1, 15);
         if (!wg2d_supported(ny, xl[0] + xl[1], yl[0] + yl[1], cls, TB)) continue;
         const WgShape sh = wg2d_shape(cls, mat);
         std::vector<TileW> t;

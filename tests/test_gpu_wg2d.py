@@ -13,14 +13,15 @@ pytestmark = pytest.mark.gpu
 
 
 def _problem(shape, npml, mat, steps=33):
-    """Random state problem; mat 0: Cb map, 1: Ca too, 2: Db too; probes on
+    """Random state problem; mat 0: Cb map, 1: and Ca, 2: and Ca and Db, 3:
+    and Db; probes on
     tile and wavefront seams; a source box across a tile seam."""
     nx, ny = shape
     pb = W.dielectric2d(nx, ny=ny, steps=steps, seed=1, nrect=6, side=(4, 24), npml=max(npml), nprobes=1,
-                        lossy=mat >= 1)
+                        lossy=mat in (1, 2))
     pb.npml = npml
     pb.cpml = dict(m=3.0, sigma_max=0.0, kappa_max=3.0, alpha_max=0.05, m_alpha=1.0)
-    if mat == 2:
+    if mat >= 2:
         pb.mu_r = np.random.default_rng(2).uniform(1, 2, shape).astype(np.float32)
     c = [(i, j) for i in (0, 1, 7, 8, 15, 16, 31, 32, nx // 2, nx - 1) for j in (0, 1, 48, 49, 63, 64, ny - 1)
          if i < nx and j < ny]
@@ -54,13 +55,13 @@ SHAPES = [((3, 5), (0, 0, 0, 0)), ((32, 64), (0, 0, 0, 0)), ((33, 65), (8, 8, 8,
           ((203, 147), (16, 16, 16, 16)), ((300, 83), (12, 0, 0, 0))]
 
 
-@pytest.mark.parametrize("mat", [0, 1, 2])
+@pytest.mark.parametrize("mat", [0, 1, 2, 3])
 @pytest.mark.parametrize("shape,npml", SHAPES)
 def test_wg2d_bits_of_the_single_step_kernel(shape, npml, mat):
     from oracle import oracle as O
     pb = _problem(shape, npml, mat)
     init = _state(shape)
-    comp = ("ez", "hx", "hy")[mat]
+    comp = ("ez", "hx", "hy", "ez")[mat]
     one = _run(pb, init, (2,), comp)
     for cls in (0, 1, 2):
         for TB in (1, 6, 15):
