@@ -310,8 +310,9 @@ int fdtd_set_material(fdtd_sim *sim, const int32_t *lo, const int32_t *hi,
  *    2D fused: tile[0] = V (1, 2 or 4 consecutive y cells per lane; ny % V
  *    must be 0), tile[1] = TX (x rows marched by one wavefront).
  *    3D fused: tile[0] = V (1, 2 or 4 consecutive z cells per thread;
- *    nz % V must be 0); tile[2] = x planes marched by one workgroup (0 =
- *    16, at most 4096); tile[1] and tile[3] must be 0.
+ *    nz % V must be 0); tile[2] = x planes marched by one workgroup (at
+ *    most 4096; 0 = one thread per cell over the whole grid up to 2^22
+ *    cells, 2^23 with V < 4, else 16 planes); tile[1] and tile[3] must be 0.
  *    3D two-step: as 3D fused with V = 4; also nz <= 512, at most 64
  *    z-CPML cells in all, and no 4-cell z group holding cells of both z
  *    slabs; tile[1] = 0 (tiles near the x/y slabs in the two-step kernel)

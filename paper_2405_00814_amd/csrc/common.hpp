@@ -246,6 +246,7 @@ struct Tile3 {
 // One launch of the fused 3D kernel over a list of tiles.
 struct Wave3DLaunch {
     int V, wpb;    // z cells per thread; wavefronts (y rows) per workgroup
+    bool flat;     // the whole grid, one thread per cell (launch_3d_flat)
     bool pxy, pz;  // CPML code for x/y slabs, z slabs
     int off, n;    // tile list entries [off, off + n) (multiple of 8)
     int64_t cells; // cells the launch updates
@@ -262,6 +263,11 @@ void wave3d_plan(int nx, int ny, int nz, const Fused3DCfg &c, const int *xlohi, 
 hipError_t launch_3d_wave(const Prob3D &p, const Wave3DPlan &pl, const Tile3 *tiles,
                           const ProbeTiles &pt, int64_t step, hipStream_t st,
                           hipEvent_t *ev = nullptr);
+// One fused step of the whole grid, one thread per cell (k3df.hip); pt:
+// probes grouped by kFlatBlock consecutive cells.  part: 0 = all cells, 1 =
+// those outside the x and y slabs, 2 = those inside.
+constexpr int kFlatBlock = 256;
+hipError_t launch_3d_flat(const Prob3D &p, const ProbeTiles &pt, int64_t step, int part, hipStream_t st);
 // Two steps per pass (temporal blocking).  A tile: planes [i0, i1), rows
 // j0 .. j0+nrows-1, full z; i0 == i1 marks padding.
 struct TileTB {

@@ -375,8 +375,29 @@ void Sim::build_probe_tiles() {
     }
     if (ndim == 3) {
         const int xl[2] = {ax[0].lo, ax[0].hi}, yl[2] = {ax[1].lo, ax[1].hi}, zl[2] = {ax[2].lo, ax[2].hi};
-        wave3d_plan(nx, ny, nz, Fused3DCfg{a, c3}, xl, yl, zl, plan3);
-        swap_in(tl_dev, dev_upload(al, plan3.tiles.data(), plan3.tiles.size(), st));
+        if (flat3d()) {
+            plan3.tiles.clear();
+            // (one launch; a per-launch profile takes the cells outside and
+            // inside the x and y slabs in one each)
+            const int64_t cx = nx - xl[0] - xl[1], cy = ny - yl[0] - yl[1], sz = zl[0] + zl[1];
+            Wave3DLaunch l{};
+            l.V = 1;
+            l.flat = true;
+            l.pz = sz > 0;
+            l.cells = cx * cy * nz;
+            l.psi = 4 * cx * cy * sz;
+            plan3.l.assign(1, l);
+            if (l.cells < ncell) {
+                l.pxy = true;
+                l.psi = -l.psi;
+                for (int q = 0; q < NPSI3; ++q) l.psi += psi_len[q];
+                l.cells = ncell - l.cells;
+                plan3.l.push_back(l);
+            }
+        } else {
+            wave3d_plan(nx, ny, nz, Fused3DCfg{a, c3}, xl, yl, zl, plan3);
+            swap_in(tl_dev, dev_upload(al, plan3.tiles.data(), plan3.tiles.size(), st));
+        }
         if (kcfg.variant == 3) {
             two3d_plan(nx, ny, nz, Fused3DCfg{a, c3}, mat, b == 0, kcfg.tile[3], cus, xl, yl, zl, plan2);
             plan2_mat = mat;
@@ -400,6 +421,9 @@ void Sim::build_probe_tiles() {
             const int i = (int)(probe_cells[q] / ny), j = (int)(probe_cells[q] % ny);
             tile[q] = fused2d_tile_of(nx, ny, c, i, j);
         }
+    } else if (flat3d()) {
+        ntiles = (int)((ncell + kFlatBlock - 1) / kFlatBlock + 7) / 8 * 8;
+        for (size_t q = 0; q < probe_cells.size(); ++q) tile[q] = (int)(probe_cells[q] / kFlatBlock);
     } else {
         ntiles = wave3d_ngroups(nx, ny);
         for (size_t q = 0; q < probe_cells.size(); ++q) {
@@ -659,11 +683,21 @@ void Sim::launch_step(int64_t step) {
                                   split2d() ? &sp : nullptr),
                   "2d fused step");
     } else {
-        hip_check(launch_3d_wave(prob3d(cur, 1 - cur), plan3, tl_dev, pt, step, st, lev), "3d fused step");
+        if (flat3d()) {
+            if (probe_cells.empty()) pt = ProbeTiles{nullptr, nullptr, nullptr};
+            const int parts = lev ? (int)plan3.l.size() : 1;
+            for (int q = 0; q < parts; ++q) {
+                if (lev) hip_check(hipEventRecord(lev[q], st), "event");
+                hip_check(launch_3d_flat(prob3d(cur, 1 - cur), pt, step, parts > 1 ? q + 1 : 0, st), "3d fused step");
+            }
+            if (lev) hip_check(hipEventRecord(lev[parts], st), "event");
+        } else {
+            hip_check(launch_3d_wave(prob3d(cur, 1 - cur), plan3, tl_dev, pt, step, st, lev), "3d fused step");
+        }
     }
     cur = 1 - cur;
     if (ndim == 3) {
-        last_launches += (int64_t)plan3.l.size();
+        last_launches += flat3d() && !lev ? 1 : (int64_t)plan3.l.size();
     } else {
         const bool pml = ax[0].lo + ax[0].hi + ax[1].lo + ax[1].hi > 0;
         last_launches += (pml && split2d()) ? (tl2_inner > 0) + (tl2_outer > 0) : 1;
@@ -954,6 +988,10 @@ constexpr int64_t kWide2DCells = (int64_t)8 << 20;
 constexpr int kTB2DefaultTX = 4;
 // smallest 3D grid (cells) on which the default takes two steps per pass
 constexpr int64_t kTwoStepMinCells = (int64_t)1 << 23;
+// planes per workgroup of the marching kernel between one thread per cell
+// and two steps per pass: with 16 its workgroups leave CUs idle (us per
+// step: 180^3 145 (168 with 16), 200^3 169 (184), without CPML 91 (103))
+constexpr int kMarchMidTX = 4;
 
 Fused2DCfg default_single2d(int nx, int ny) {
     const bool wide = (int64_t)nx * ny >= kWide2DCells && ny % 2 == 0;
@@ -1007,6 +1045,7 @@ int default_variant_tiles(const Sim &s, fdtd_kernel_config &k) {
                              two3d_supported(s.nx, s.ny, s.nz, s.ax[2].lo, s.ax[2].hi);
             k.variant = two ? 3 : 2;
             k.tile[0] = c.V;
+            if (c.V == 4 && s.ncell > kFlatMaxCells4 && s.ncell < kTwoStepMinCells) k.tile[2] = kMarchMidTX;
             return 0;
         }
     }
@@ -2086,12 +2125,13 @@ int fdtd_autotune(fdtd_sim *sim, int32_t trial_steps, fdtd_kernel_config *out) {
                         k.tile[0] = V;
                         k.tile[1] = TX;
                         k.tile[2] = TB;
+                if (TX == 0 && V != 1) continue;  // one thread per cell, whatever V
                         k.tile[3] = TXo;
                         k.tb = 1;
                         if (config_ok(s, k)) cand.push_back(k);
                     }
     } else {
-        for (int TX : {8, 16, 32})
+        for (int TX : {0, kMarchMidTX, 8, 16, 32})
             for (int V : {1, 2, 4}) {
                 fdtd_kernel_config k{};
                 k.variant = 2;

@@ -37,6 +37,14 @@ struct DevAlloc {
 };
 
 // One axis of CPML tables in double precision before rounding.
+// Largest 3D grid whose single steps take one thread per cell, where four
+// cells per thread would do and where they would not (rows not a multiple
+// of 4).  Measured against the marching kernel, us per step with CPML:
+// 60x50x64 7.2 (its default chunk 105, its best 15), 100x90x84 19 (118, 28),
+// 125x116x144 40 (117, 54), 160^3 90 (142, 100), 199x133x136 57 (114, 77),
+// 200^3 193 (184), 201x199x197 198 (235).
+constexpr int64_t kFlatMaxCells4 = (int64_t)1 << 22, kFlatMaxCells = (int64_t)1 << 23;
+
 struct AxisHost {
     int n = 0, lo = 0, hi = 0;
     std::vector<float> kE, bE, cE, kH, bH, cH;
@@ -146,6 +154,8 @@ struct Sim {
     // 3D fused: launch plan and its tile lists on the device
     Wave3DPlan plan3;
     Tile3 *tl_dev = nullptr;
+    // 3D fused, tile[2] = 0: one thread per cell on grids the caches hold
+    bool flat3d() const { return ndim == 3 && kcfg.variant == 2 && kcfg.tile[2] == 0 && ncell <= (kcfg.tile[0] == 4 ? kFlatMaxCells4 : kFlatMaxCells); }
     // the maps as the workgroup tiles count them (3: Db without Ca)
     int wmat() const { return mumap && !lossy ? 3 : mat(); }
     // 3D two steps per pass (variant 3): its plan and tile lists
