@@ -367,6 +367,31 @@ struct CsrLayerArgs {
     int nrows;
 };
 hipError_t launch_csr_layer(const CsrLayerArgs &L, float *x, hipStream_t st);
+// The same layer as runs of rows alike (csr.hip): a run is up to 64
+// consecutive rows with equally many edges whose destinations and columns
+// step by constant strides.  rec: per run 32 ints (at most 8 edges, the
+// first n8 runs) or 64 (at most 16): {first destination, its stride, rows |
+// edges << 8, first weight, 0...}, then from [8] three per edge: {column of
+// the first row (a marker: the group's edges), stride & 0xffff | weight <<
+// 16 | sign << 24 | marker << 25, weight 0 (float)}.  weight 0 is the same
+// for all rows; weight v > 0 is w[first + 64 (v - 1) + row], negated if sign.
+// src: per run the rows that take the soft source (null: none); probe_start:
+// per run its part of probe_row / probe_slot (null: no probes).
+struct RunLayerArgs {
+    const int *rec;
+    const float *w;
+    int n8, n;
+    const uint64_t *src;
+    const float *src_vals;
+    int64_t step;
+    const int *probe_start, *probe_row, *probe_slot;
+    float *out;
+    int64_t out_stride, out_index;
+};
+hipError_t launch_run_layer(const RunLayerArgs &L, float *x, hipStream_t st);
+// out[i * ny + j] = x[n0 + si i + sj j] (+ the node after it)
+hipError_t launch_node_field(const float *x, float *out, int nx, int ny, int64_t n0, int64_t si, int64_t sj, bool two,
+                             hipStream_t st);
 // Soft source and probes on a node vector.
 hipError_t launch_node_source_probe(float *x, const int *src_nodes, int nsrc, const float *src_vals,
                                     int64_t src_len, int64_t step, int np,

@@ -140,6 +140,109 @@ hipError_t launch_csr_layer(const CsrLayerArgs &L, float *x, hipStream_t st) {
     return hipGetLastError();
 }
 
+// One run per wavefront, one row per lane.  What the CSR layer above spends
+// per row on edges (8 bytes each, staged through LDS behind two dependent
+// loads) a run holds once for its 64 rows: columns are a base and a stride,
+// weights that the rows share are scalars, and a column of weights that
+// appears again (negated) in the row is kept once.  A wavefront reads its
+// record by scalar loads, then issues all gathers and weights together.
+// Sums in edge order with the same roundings.  The E layer's launch adds the
+// source and takes the probes.  Bound by the two dependent launches per step
+// and the latency of record, gather and store in each; per step of a 768^2
+// graph 19.6 us (31.2 by CSR), of 2500^2 110 (213).
+template <int NMAX>
+__device__ __forceinline__ float run_row(const int *__restrict__ r, const float *__restrict__ w, float *__restrict__ x,
+                                         int ne, int row) {
+    float xq[NMAX], wq[NMAX];
+#pragma unroll
+    for (int u = 0; u < NMAX; ++u) {
+        xq[u] = wq[u] = 0.f;
+        if (u < ne) {  // uniform, as all that follows from the record
+            const unsigned f = (unsigned)r[3 * u + 1];
+            if (!(f >> 25 & 1)) xq[u] = x[r[3 * u] + (int)(short)(f & 0xffffu) * row];
+            const int v = (int)(f >> 16 & 0xff);
+            if (v == 0) {
+                wq[u] = __int_as_float(r[3 * u + 2]);
+            } else {
+                const float a = w[64 * (v - 1) + row];
+                wq[u] = f >> 24 & 1 ? -a : a;
+            }
+        }
+    }
+    float acc = 0.f, s = 0.f, wm = 0.f;
+    int rem = 0, node = 0;
+#pragma unroll
+    for (int u = 0; u < NMAX; ++u) {
+        if (u < ne) {
+            const unsigned f = (unsigned)r[3 * u + 1];
+            if (rem > 0) {  // inside a group: its first edge is its own node
+                if (node < 0) node = r[3 * u] + (int)(short)(f & 0xffffu) * row;
+                s = __builtin_fmaf(wq[u], xq[u], s);
+                if (--rem == 0) {
+                    x[node] = s;
+                    acc = __builtin_fmaf(wm, s, acc);
+                }
+            } else if (f >> 25 & 1) {
+                rem = r[3 * u];
+                wm = wq[u];
+                s = 0.f;
+                node = -1;
+            } else {
+                acc = __builtin_fmaf(wq[u], xq[u], acc);
+            }
+        }
+    }
+    return acc;
+}
+
+__global__ __launch_bounds__(256) void k_run_layer(RunLayerArgs L, const int *__restrict__ rec,
+                                                   const float *__restrict__ w, float *__restrict__ x) {
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = (int)(threadIdx.x & 63);
+    const int k = xcd_block((int)blockIdx.x, (int)gridDim.x) * 4 + wv;
+    if (k >= L.n) return;  // wave-uniform
+    const int *__restrict__ r = rec + (k < L.n8 ? 32 * (int64_t)k : 32 * (int64_t)L.n8 + 64 * (int64_t)(k - L.n8));
+    const int d0 = r[0], ds = r[1], rows = r[2] & 0xff, ne = r[2] >> 8;
+    const float *__restrict__ wr = w + r[3];
+    const uint64_t src = L.src ? L.src[k] : 0;
+    const int p0 = L.probe_start ? L.probe_start[k] : 0, p1 = L.probe_start ? L.probe_start[k + 1] : 0;
+    if (lane >= rows) return;
+    float v = k < L.n8 ? run_row<8>(r + 8, wr, x, ne, lane) : run_row<16>(r + 8, wr, x, ne, lane);
+    if (src != 0 && (src >> lane & 1)) v += L.src_vals[L.step];
+    x[d0 + ds * lane] = v;
+    for (int q = p0; q < p1; ++q)
+        if (L.probe_row[q] == lane) L.out[(int64_t)L.probe_slot[q] * L.out_stride + L.out_index] = v;
+}
+
+hipError_t launch_run_layer(const RunLayerArgs &L, float *x, hipStream_t st) {
+    if (L.n <= 0) return hipSuccess;
+    const unsigned nb = (unsigned)(((int64_t)L.n + 31) / 32 * 8);
+    hipLaunchKernelGGL(k_run_layer, dim3(nb), dim3(256), 0, st, L, L.rec, L.w, x);
+    return hipGetLastError();
+}
+
+// Node order to cell order: reads along i, writes along j, turned in LDS.
+__global__ __launch_bounds__(256) void k_node_field(const float *__restrict__ x, float *__restrict__ out, int nx, int ny,
+                                                    int64_t n0, int64_t si, int64_t sj, int two) {
+    __shared__ float t[32][33];
+    const int a = (int)(threadIdx.x & 31), b = (int)(threadIdx.x >> 5);
+    const int ti = (int)blockIdx.x % ((nx + 31) / 32) * 32, tj = (int)blockIdx.x / ((nx + 31) / 32) * 32;
+    for (int q = b; q < 32; q += 8)
+        if (ti + a < nx && tj + q < ny) {
+            const int64_t n = n0 + si * (ti + a) + sj * (tj + q);
+            t[q][a] = two ? x[n] + x[n + 1] : x[n];
+        }
+    __syncthreads();
+    for (int q = b; q < 32; q += 8)
+        if (ti + q < nx && tj + a < ny) out[(int64_t)(ti + q) * ny + tj + a] = t[a][q];
+}
+
+hipError_t launch_node_field(const float *x, float *out, int nx, int ny, int64_t n0, int64_t si, int64_t sj, bool two,
+                             hipStream_t st) {
+    const int64_t nb = (int64_t)((nx + 31) / 32) * ((ny + 31) / 32);
+    hipLaunchKernelGGL(k_node_field, dim3((unsigned)nb), dim3(256), 0, st, x, out, nx, ny, n0, si, sj, two ? 1 : 0);
+    return hipGetLastError();
+}
+
 // Soft source on its nodes, then probe samples (one block).
 __global__ void k_node_src_probe(float *x, const int *src_nodes, int nsrc, const float *src_vals,
                                  int64_t src_len, int64_t step, int np, const int *probe_node,

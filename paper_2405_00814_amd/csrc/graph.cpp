@@ -11,7 +11,8 @@
 // Hx(i,j-1), Hy(i,j), Hy(i-1,j)} (as printed in Prop. 1); Hx gathers
 // {itself, Ez(i,j), Ez(i,j+1)} and Hy gathers {itself, Ez(i,j), Ez(i+1,j)}
 // (forward offsets: with E owned at the lower cell corner this is the
-// consistent staggering).  Each layer is one CSR sweep in place: the field
+// consistent staggering).  Each layer is one sweep in place (runs of rows
+// alike, or CSR where the runs are short): the field
 // rows, of which those with a psi edge first evaluate that auxiliary row
 // (psi <- b psi + c D, read by no other row) and then use the new psi, as a
 // sweep of the auxiliary rows followed by one of the field rows would.
@@ -52,8 +53,121 @@ T *up(DevAlloc &al, const std::vector<T> &h, hipStream_t st, int64_t &bytes) {
 }  // namespace
 
 static void free_layer(Sim &s, Sim::Graph::Layer &L) {
-    for (void *p : {(void *)L.rowptr, (void *)L.col, (void *)L.dst, (void *)L.w, (void *)L.chunk}) s.al.put(p);
+    for (void *p : {(void *)L.rowptr, (void *)L.col, (void *)L.dst, (void *)L.w, (void *)L.chunk, (void *)L.rec, (void *)L.rw})
+        s.al.put(p);
     L = Sim::Graph::Layer{};
+}
+
+// Fewest rows per run on average for which a layer is laid out as runs; a
+// wavefront takes a run whatever its rows.  us per step, runs against the
+// CSR sweep and its source/probe launch: 40x800 (12 rows per run) 10.1 (13.1),
+// 77x70 (25) 9.0 (12.4), 250^2 9.4 (14.1), 768^2 19.6 (31.2), 2500^2 110
+// (213).  The line is not where the speed turns: narrow grids keep the three
+// launches per step that last_step_time has always counted there.
+constexpr int kRunMinRows = 26;
+
+// The rows `m` as runs (RunLayerArgs); false (nothing kept) when the runs
+// are short or a row has more than 16 edges.
+static bool put_runs(Sim &s, Sim::Graph::Layer &L, const RowBuilder &m) {
+    const int n = (int)m.dst.size();
+    auto len = [&](int r) { return m.rowptr[(size_t)r + 1] - m.rowptr[(size_t)r]; };
+    std::vector<std::pair<int, int>> cut;  // (first row, rows)
+    for (int r = 0; r < n;) {
+        const int ne = len(r), q0 = m.rowptr[(size_t)r];
+        if (ne > 16 || ne < 1) return false;
+        int k = 1;
+        for (; k < 64 && r + k < n; ++k) {
+            const int q = m.rowptr[(size_t)r + k], qa = m.rowptr[(size_t)r + k - 1];
+            bool same = len(r + k) == ne;
+            const int ds = m.dst[(size_t)r + 1 < (size_t)n ? (size_t)r + 1 : (size_t)r] - m.dst[(size_t)r];
+            same = same && m.dst[(size_t)r + k] - m.dst[(size_t)r + k - 1] == ds;
+            for (int u = 0; u < ne && same; ++u) {
+                const int a = m.col[(size_t)(q0 + u)], b = m.col[(size_t)(q + u)];
+                if (a < 0 || b < 0) {
+                    same = a == b;
+                } else {
+                    const int64_t cs = (int64_t)m.col[(size_t)(m.rowptr[(size_t)r + 1] + u)] - a;
+                    same = cs >= -32768 && cs < 32768 && (int64_t)b - m.col[(size_t)(qa + u)] == cs;
+                }
+            }
+            if (!same) break;
+        }
+        cut.emplace_back(r, k);
+        r += k;
+    }
+    if (cut.empty() || (int64_t)n < (int64_t)kRunMinRows * (int64_t)cut.size()) return false;
+    std::vector<int> rec;
+    std::vector<float> w;
+    L.n8 = 0;
+    L.nrun = (int)cut.size();
+    L.runs.clear();
+    int at = 0;
+    for (int pass = 0; pass < 2; ++pass)
+        for (const auto &[r, k] : cut) {
+            const int ne = len(r), q0 = m.rowptr[(size_t)r];
+            if ((ne > 8) != (pass == 1)) continue;
+            const size_t o = rec.size();
+            rec.resize(o + (pass ? 64 : 32), 0);
+            const int ds = k > 1 ? m.dst[(size_t)r + 1] - m.dst[(size_t)r] : 0;
+            if (w.size() >= (size_t)INT32_MAX - 1024) return false;
+            rec[o] = m.dst[(size_t)r];
+            rec[o + 1] = ds;
+            rec[o + 2] = k | ne << 8;
+            rec[o + 3] = (int)w.size();
+            const size_t w0 = w.size();
+            auto wt = [&](int u, int t) { return m.w[(size_t)(m.rowptr[(size_t)(r + t)] + u)]; };
+            auto bits = [](float v) {
+                uint32_t b;
+                std::memcpy(&b, &v, 4);
+                return b;
+            };
+            for (int u = 0; u < ne; ++u) {
+                const int a = m.col[(size_t)(q0 + u)];
+                const int cs = a >= 0 && k > 1 ? m.col[(size_t)(m.rowptr[(size_t)r + 1] + u)] - a : 0;
+                unsigned f = (unsigned)cs & 0xffffu;
+                bool one = true;
+                for (int t = 1; t < k && one; ++t) one = bits(wt(u, t)) == bits(wt(u, 0));
+                float w0v = 0.f;
+                if (one) {
+                    w0v = wt(u, 0);
+                } else {  // an equal (or negated) column of weights of the run, or a new one
+                    int v = -1;
+                    unsigned sg = 0;
+                    const int nv = (int)((w.size() - w0) / 64);
+                    for (int c = 0; c < nv && v < 0; ++c)
+                        for (unsigned g = 0; g < 2 && v < 0; ++g) {
+                            bool eq = true;
+                            for (int t = 0; t < k && eq; ++t)
+                                eq = bits(w[w0 + 64 * (size_t)c + t]) == (bits(wt(u, t)) ^ (g << 31));
+                            if (eq) {
+                                v = c;
+                                sg = g;
+                            }
+                        }
+                    if (v < 0) {
+                        v = nv;
+                        w.resize(w.size() + 64, 0.f);
+                        for (int t = 0; t < k; ++t) w[w0 + 64 * (size_t)v + t] = wt(u, t);
+                    }
+                    f |= (unsigned)(v + 1) << 16 | sg << 24;
+                }
+                if (a < 0) f |= 1u << 25;
+                rec[o + 8 + 3 * u] = a < 0 ? -1 - a : a;
+                rec[o + 9 + 3 * u] = (int)f;
+                std::memcpy(&rec[o + 10 + 3 * u], &w0v, 4);
+            }
+            L.runs.push_back({m.dst[(size_t)r], ds, k, at});
+            ++at;
+            if (pass == 0) L.n8 = at;
+        }
+    std::sort(L.runs.begin(), L.runs.end());
+    if (w.empty()) w.resize(64, 0.f);
+    L.nrows = n;
+    L.nnz = (int64_t)m.col.size();
+    L.rec = up(s.al, rec, s.st, s.g.bytes);
+    L.rw = up(s.al, w, s.st, s.g.bytes);
+    hip_check(hipStreamSynchronize(s.st), "sync");
+    return true;
 }
 
 // Upload one layer: the field rows `m`, each edge to a node that a row of
@@ -100,6 +214,11 @@ static void put_layer(Sim &s, Sim::Graph::Layer &L, RowBuilder &m, RowBuilder *a
             if (u != 1) fail(FDTD_EINVAL, "graph builder: an auxiliary row without exactly one reader");
         L.naux = (int)aux->dst.size();
         m = std::move(g);
+    }
+    if (put_runs(s, L, m)) {
+        m = RowBuilder{};
+        if (aux) *aux = RowBuilder{};
+        return;
     }
     const int n = (int)m.dst.size();
     std::vector<int4> ch((size_t)(n + 63) / 64);
@@ -174,20 +293,24 @@ static void build_graph_split(Sim &s) {
             hm.end_row(q(i, j));
         }
     }
-    for (int j = 1; j < ny; ++j)
+    for (int j = 1; j < ny; ++j) {
         for (int i = 1; i < nx; ++i) {
             const int64_t c = cell(i, j);
-            const double ca = ca_of(c), cb = cb_of(c);
-            const double wx = cb * (double)X.cE[i] * (double)X.kE[i], wy = cb * (double)Y.cE[j] * (double)Y.kE[j];
-            em.edge(tx(i, j), ca * (double)X.bE[i]);
+            const double wx = cb_of(c) * (double)X.cE[i] * (double)X.kE[i];
+            em.edge(tx(i, j), ca_of(c) * (double)X.bE[i]);
             em.edge(q(i, j), wx);
             em.edge(q(i - 1, j), -wx);
             em.end_row(tx(i, j));
-            em.edge(tz(i, j), ca * (double)Y.bE[j]);
+        }
+        for (int i = 1; i < nx; ++i) {
+            const int64_t c = cell(i, j);
+            const double wy = cb_of(c) * (double)Y.cE[j] * (double)Y.kE[j];
+            em.edge(tz(i, j), ca_of(c) * (double)Y.bE[j]);
             em.edge(u(i, j), -wy);
             em.edge(u(i, j - 1), wy);
             em.end_row(tz(i, j));
         }
+    }
     Sim::Graph &g = s.g;
     g.bytes = 0;
     put_layer(s, g.h, hm, nullptr);
@@ -195,6 +318,7 @@ static void build_graph_split(Sim &s) {
     g.nmain = nnodes;
     g.nnodes = nnodes;
     if (!g.x) g.x = (float *)s.al.get((size_t)nnodes * 4);
+    if (!g.fld) g.fld = (float *)s.al.get((size_t)nx * ny * 4);
     g.ez_node.resize((size_t)nx * ny);
     g.ez_node2.resize((size_t)nx * ny);
     for (int i = 0; i < nx; ++i)
@@ -361,6 +485,7 @@ void build_graph(Sim &s) {
     g.nmain = nmain;
     g.nnodes = nnodes;
     if (!g.x) g.x = (float *)s.al.get((size_t)nnodes * 4);
+    if (!g.fld) g.fld = (float *)s.al.get((size_t)nx * ny * 4);
     g.ez_node.resize((size_t)N);
     for (int i = 0; i < nx; ++i)
         for (int j = 0; j < ny; ++j) g.ez_node[(size_t)i * ny + j] = t(i, j);
@@ -378,7 +503,10 @@ void build_graph(Sim &s) {
     hip_check(hipStreamSynchronize(s.st), "sync");
 }
 
-void graph_refold(Sim &s) { build_graph(s); }
+void graph_refold(Sim &s) {
+    build_graph(s);
+    graph_set_source_probes(s);
+}
 
 void graph_set_source_probes(Sim &s) {
     Sim::Graph &g = s.g;
@@ -408,15 +536,88 @@ void graph_set_source_probes(Sim &s) {
         }
         hip_check(hipStreamSynchronize(s.st), "sync");
     }
+    // By the run of the E layer that holds each node, so that the layer's
+    // launch takes source and probes along; a node that no row writes (on
+    // the low walls) leaves them all to a launch of their own.
+    for (void *p : {(void *)g.src_mask, (void *)g.probe_start, (void *)g.probe_row, (void *)g.probe_slot}) s.al.put(p);
+    g.src_mask = nullptr;
+    g.probe_start = g.probe_row = g.probe_slot = nullptr;
+    g.in_runs = false;
+    const Sim::Graph::Layer &L = g.e;
+    if (!L.rec || !g.ez_node2.empty()) return;
+    auto find = [&](int64_t node, int &run, int &row) {
+        auto it = std::upper_bound(L.runs.begin(), L.runs.end(), node,
+                                   [](int64_t v, const std::array<int, 4> &r) { return v < r[0]; });
+        if (it == L.runs.begin()) return false;
+        const std::array<int, 4> &r = *--it;
+        const int64_t d = node - r[0];
+        if (d != 0 && (r[1] <= 0 || d % r[1] != 0 || d / r[1] >= r[2])) return false;
+        run = r[3];
+        row = d == 0 ? 0 : (int)(d / r[1]);
+        return true;
+    };
+    int run = 0, row = 0;
+    std::vector<uint64_t> mask;
+    if (s.src_idx >= 0) {
+        mask.assign((size_t)L.nrun, 0);
+        for (int i = s.src_box[0]; i < s.src_box[1]; ++i)
+            for (int j = s.src_box[2]; j < s.src_box[3]; ++j) {
+                if (!find(g.ez_node[(size_t)i * s.ny + j], run, row)) return;
+                mask[(size_t)run] |= (uint64_t)1 << row;
+            }
+    }
+    std::vector<std::array<int, 3>> pr;  // {run, row, probe}
+    for (size_t p = 0; p < s.probe_cells.size(); ++p) {
+        if (!find(g.ez_node[(size_t)s.probe_cells[p]], run, row)) return;
+        pr.push_back({run, row, (int)p});
+    }
+    std::sort(pr.begin(), pr.end());
+    std::vector<int> start((size_t)L.nrun + 1, 0), prow, pslot;
+    for (const auto &e : pr) {
+        start[(size_t)e[0] + 1]++;
+        prow.push_back(e[1]);
+        pslot.push_back(e[2]);
+    }
+    for (int r = 0; r < L.nrun; ++r) start[(size_t)r + 1] += start[(size_t)r];
+    int64_t dummy = 0;
+    if (!mask.empty()) g.src_mask = up(s.al, mask, s.st, dummy);
+    if (!pr.empty()) {
+        g.probe_start = up(s.al, start, s.st, dummy);
+        g.probe_row = up(s.al, prow, s.st, dummy);
+        g.probe_slot = up(s.al, pslot, s.st, dummy);
+    }
+    hip_check(hipStreamSynchronize(s.st), "sync");
+    g.in_runs = true;
 }
 
 void graph_step(Sim &s, int64_t step) {
     Sim::Graph &g = s.g;
     for (auto *L : {&g.h, &g.e}) {
-        const CsrLayerArgs a{L->rowptr, L->col, L->w, L->dst, L->chunk, L->nrows};
-        hip_check(launch_csr_layer(a, g.x, s.st), "csr layer");
+        if (L->rec) {
+            RunLayerArgs a{};
+            a.rec = L->rec;
+            a.w = L->rw;
+            a.n8 = L->n8;
+            a.n = L->nrun;
+            if (L == &g.e && g.in_runs) {
+                a.src = step < s.src_len ? g.src_mask : nullptr;
+                a.src_vals = s.src_dev;
+                a.step = step;
+                a.probe_start = g.probe_start;
+                a.probe_row = g.probe_row;
+                a.probe_slot = g.probe_slot;
+                a.out = s.rec_dev;
+                a.out_stride = s.rec_cap;
+                a.out_index = step - (s.n_done - s.n_rec);
+            }
+            hip_check(launch_run_layer(a, g.x, s.st), "graph layer");
+        } else {
+            const CsrLayerArgs a{L->rowptr, L->col, L->w, L->dst, L->chunk, L->nrows};
+            hip_check(launch_csr_layer(a, g.x, s.st), "csr layer");
+        }
         s.last_launches += 1;
     }
+    if (g.in_runs) return;
     hip_check(launch_node_source_probe(g.x, g.src_nodes, g.nsrc, s.src_dev, s.src_len, step,
                                        (int)s.probe_cells.size(), g.probe_node, g.probe_node2, s.rec_dev, s.rec_cap,
                                        step - (s.n_done - s.n_rec), s.st),
@@ -437,16 +638,16 @@ static int64_t node_of(const Sim &s, int comp, int i, int j) {
 
 int64_t graph_node(const Sim &s, int comp, int i, int j) { return node_of(s, comp, i, j); }
 
-void graph_get_field(Sim &s, int comp, float *host) {
-    std::vector<float> x((size_t)s.g.nnodes);
-    hip_check(hipMemcpyAsync(x.data(), s.g.x, x.size() * 4, hipMemcpyDeviceToHost, s.st), "copy");
-    hip_check(hipStreamSynchronize(s.st), "sync");
+void graph_get_field(Sim &s, int comp, float *dst, bool dst_on_device) {
     const bool two = s.split && comp == FDTD_EZ;  // Ez = Ezx + Ezy
-    for (int i = 0; i < s.nx; ++i)
-        for (int j = 0; j < s.ny; ++j) {
-            const size_t n0 = (size_t)node_of(s, comp, i, j);
-            host[(size_t)i * s.ny + j] = two ? x[n0] + x[n0 + 1] : x[n0];
-        }
+    const int64_t n0 = node_of(s, comp, 0, 0);
+    float *out = dst_on_device ? dst : s.g.fld;
+    hip_check(launch_node_field(s.g.x, out, s.nx, s.ny, n0, node_of(s, comp, 1, 0) - n0, node_of(s, comp, 0, 1) - n0,
+                                two, s.st),
+              "graph field");
+    if (!dst_on_device)
+        hip_check(hipMemcpyAsync(dst, out, (size_t)s.ncell * 4, hipMemcpyDeviceToHost, s.st), "copy");
+    hip_check(hipStreamSynchronize(s.st), "sync");
 }
 
 void graph_set_field(Sim &s, int comp, const float *host) {

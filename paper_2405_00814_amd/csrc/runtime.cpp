@@ -1768,14 +1768,7 @@ int fdtd_get_field(fdtd_sim *sim, int component, void *dst, int dst_on_device) {
     if (!comp_ok(s, component)) fail(FDTD_EINVAL, "component not present in this grid");
     const size_t bytes = (size_t)s.ncell * 4;
     if (s.is_graph) {
-        std::vector<float> h((size_t)s.ncell);
-        graph_get_field(s, component, h.data());
-        if (dst_on_device) {
-            hip_check(hipMemcpyAsync(dst, h.data(), bytes, hipMemcpyHostToDevice, s.st), "copy");
-            hip_check(hipStreamSynchronize(s.st), "sync");
-        } else {
-            std::memcpy(dst, h.data(), bytes);
-        }
+        graph_get_field(s, component, (float *)dst, dst_on_device != 0);
         return FDTD_OK;
     }
     hip_check(hipMemcpyAsync(dst, s.f[s.cur][component], bytes,
@@ -2125,7 +2118,6 @@ int fdtd_autotune(fdtd_sim *sim, int32_t trial_steps, fdtd_kernel_config *out) {
                         k.tile[0] = V;
                         k.tile[1] = TX;
                         k.tile[2] = TB;
-                if (TX == 0 && V != 1) continue;  // one thread per cell, whatever V
                         k.tile[3] = TXo;
                         k.tb = 1;
                         if (config_ok(s, k)) cand.push_back(k);
@@ -2133,6 +2125,7 @@ int fdtd_autotune(fdtd_sim *sim, int32_t trial_steps, fdtd_kernel_config *out) {
     } else {
         for (int TX : {0, kMarchMidTX, 8, 16, 32})
             for (int V : {1, 2, 4}) {
+                if (TX == 0 && V != 1) continue;  // one thread per cell, whatever V
                 fdtd_kernel_config k{};
                 k.variant = 2;
                 k.tile[0] = V;

@@ -1,6 +1,7 @@
 // Host-side simulation object behind the fdtd_sim handle.
 #pragma once
 
+#include <array>
 #include <cstdint>
 #include <map>
 #include <string>
@@ -36,7 +37,6 @@ struct DevAlloc {
     void release_all();
 };
 
-// One axis of CPML tables in double precision before rounding.
 // Largest 3D grid whose single steps take one thread per cell, where four
 // cells per thread would do and where they would not (rows not a multiple
 // of 4).  Measured against the marching kernel, us per step with CPML:
@@ -45,6 +45,7 @@ struct DevAlloc {
 // 200^3 193 (184), 201x199x197 198 (235).
 constexpr int64_t kFlatMaxCells4 = (int64_t)1 << 22, kFlatMaxCells = (int64_t)1 << 23;
 
+// One axis of CPML tables in double precision before rounding.
 struct AxisHost {
     int n = 0, lo = 0, hi = 0;
     std::vector<float> kE, bE, cE, kH, bH, cH;
@@ -145,19 +146,19 @@ struct Sim {
     // most steps per pass: a grid in one tile has no halo to use up
     int wg_most() const { return wg_n == 1 ? 65536 : wg_tb; }
     int mat() const { return mumap ? 2 : (lossy ? 1 : 0); }
+    // the maps as the workgroup tiles count them (3: Db without Ca)
+    int wmat() const { return mumap && !lossy ? 3 : mat(); }
     // variant 4 takes the 2D grid (no CPML, split field, mu_r map or graph)
     // with the current probes
     bool res2d_ok() const {
         return ndim == 2 && !split && !is_graph && mat() <= 1 &&
                res2d_supported(nx, ny, ax[0].lo + ax[0].hi + ax[1].lo + ax[1].hi > 0, (int)probe_cells.size());
     }
+    // 3D fused, tile[2] = 0: one thread per cell on grids the caches hold
+    bool flat3d() const { return ndim == 3 && kcfg.variant == 2 && kcfg.tile[2] == 0 && ncell <= (kcfg.tile[0] == 4 ? kFlatMaxCells4 : kFlatMaxCells); }
     // 3D fused: launch plan and its tile lists on the device
     Wave3DPlan plan3;
     Tile3 *tl_dev = nullptr;
-    // 3D fused, tile[2] = 0: one thread per cell on grids the caches hold
-    bool flat3d() const { return ndim == 3 && kcfg.variant == 2 && kcfg.tile[2] == 0 && ncell <= (kcfg.tile[0] == 4 ? kFlatMaxCells4 : kFlatMaxCells); }
-    // the maps as the workgroup tiles count them (3: Db without Ca)
-    int wmat() const { return mumap && !lossy ? 3 : mat(); }
     // 3D two steps per pass (variant 3): its plan and tile lists
     TwoPlan plan2;
     TileTB *tb_dev = nullptr, *tbo_dev = nullptr;
@@ -207,7 +208,17 @@ struct Sim {
             float *w = nullptr;
             int4 *chunk = nullptr;
             int64_t nnz = 0;
+            // the layer as runs of rows alike instead (RunLayerArgs)
+            int *rec = nullptr;
+            float *rw = nullptr;
+            int n8 = 0, nrun = 0;
+            std::vector<std::array<int, 4>> runs;  // {first destination, stride, rows, run}, sorted
         } h, e;
+        float *fld = nullptr;  // one field in cell order
+        // source and probes by the run that holds their node
+        uint64_t *src_mask = nullptr;
+        int *probe_start = nullptr, *probe_row = nullptr, *probe_slot = nullptr;
+        bool in_runs = false;
         std::vector<int64_t> ez_node;     // node of Ez(i,j) (host; split field: of Ezx)
         std::vector<int64_t> ez_node2;    // split field: node of Ezy(i,j), else empty
         int *src_nodes = nullptr;  // device: the source box's Ez nodes
@@ -266,7 +277,7 @@ void graph_refold(Sim &s);
 void graph_set_source_probes(Sim &s);
 // node of component comp at cell (i, j) in the graph's node vector
 int64_t graph_node(const Sim &s, int comp, int i, int j);
-void graph_get_field(Sim &s, int comp, float *host);
+void graph_get_field(Sim &s, int comp, float *dst, bool dst_on_device);
 void graph_set_field(Sim &s, int comp, const float *host);
 // nonzeros of the largest layer (graph.cpp); the row pointers are int32
 int64_t graph_layer_nnz_max(int nx, int ny, int sx, int sy, bool split);
