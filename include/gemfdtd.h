@@ -319,8 +319,8 @@ int fdtd_set_material(fdtd_sim *sim, const int32_t *lo, const int32_t *hi,
  *    or 1 (as two single steps); tile[2] = x planes per interior tile (0:
  *    with tile[1] = 0, the length whose tile list a model of the
  *    device's dispatch finishes first, 16 .. 128; with tile[1] = 1, 16);
- *    tile[3] = x planes per tile of the tiles near the x/y slabs (0 = 16,
- *    at most 4096).
+ *    tile[3] = x planes per tile of the tiles near the x/y slabs (at most
+ *    4096; 0: the length of 4 .. 16 chosen likewise).
  *    2D multi-step (variant 3 on a 2D grid): tile[0] = V (1, 2 or 4; ny % V
  *    must be 0; 0 = 1), tile[1] = TX (rows per tile, 1..65536; 0 = 4), tile[2] =
  *    TB (leapfrog steps per pass: 2 or 4; 0 = 4), tile[3] = rows per tile

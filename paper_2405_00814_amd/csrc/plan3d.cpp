@@ -306,52 +306,90 @@ void two3d_plan(int nx, int ny, int nz, const Fused3DCfg &c, int mat, bool slab_
         // launch with it: x chunks of TXo planes over the whole x range,
         // bands of rows_o rows over every row of an x-slab chunk and over
         // [0, ya), [yb, ny) of the others
-        const int TXo = txo > 0 ? txo : 16, Ro = pl.rows_o;
-        chunks(xo, 0, xa, TXo);
-        const size_t nlo = xo.size();
-        chunks(xo, xa, xb, TXo);
-        const size_t nmid = xo.size();
-        chunks(xo, xb, nx, TXo);
+        const int Ro = pl.rows_o;
         std::vector<TileTB> kind[3];  // cones touching both slab kinds, x slabs only, y slabs only
-        for (size_t q = 0; q < xo.size(); ++q) {
-            const int i0 = xo[q].a, i1 = xo[q].b;
-            int64_t xs = 0;
-            for (int i = i0; i < i1; ++i) xs += inslab(nx, xlohi[0], xlohi[1], i);
-            auto band = [&](int a, int b) {
-                for (int j0 = a; j0 < b; j0 += Ro) {
-                    const int nr = std::min(Ro, b - j0);
-                    int64_t ysn = 0;
-                    for (int jj = j0; jj < j0 + nr; ++jj) ysn += inslab(ny, ylohi[0], ylohi[1], jj);
-                    const bool onx = !clear(nx, xlohi[0], xlohi[1], i0 - 2, i1);
-                    const bool ony = !clear(ny, ylohi[0], ylohi[1], j0 - 2, j0 + nr);
-                    kind[onx && ony ? 0 : (ony ? 2 : 1)].push_back(TileTB{i0, i1, j0, nr});
-                    pl.tbo_cells += (int64_t)(i1 - i0) * nr * nz;
-                    pl.tbo_psi += 4 * (xs * nr * nz + (int64_t)(i1 - i0) * ysn * nz + (int64_t)(i1 - i0) * nr * zs);
-                }
-            };
-            if (q < nlo || q >= nmid) {
-                band(0, ny);
-            } else {
-                band(0, ya);
-                band(yb, ny);
-            }
-        }
         // the tiles near both slab kinds, then those near one kind: the
         // launch hands each XCD a contiguous eighth of its list, so each
         // eighth takes an eighth of the x-slab tiles and an eighth of the
-        // y-slab ones (their chunk lengths differ), padded to a common length
+        // y-slab ones (their chunk lengths differ)
+        std::vector<std::vector<TileTB>> part(8);
+        auto lay = [&](int TXo) {
+            xo.clear();
+            for (auto &k : kind) k.clear();
+            for (auto &q : part) q.clear();
+            chunks(xo, 0, xa, TXo);
+            const size_t nlo = xo.size();
+            chunks(xo, xa, xb, TXo);
+            const size_t nmid = xo.size();
+            chunks(xo, xb, nx, TXo);
+            for (size_t q = 0; q < xo.size(); ++q) {
+                const int i0 = xo[q].a, i1 = xo[q].b;
+                const bool onx = !clear(nx, xlohi[0], xlohi[1], i0 - 2, i1);
+                auto band = [&](int a, int b) {
+                    for (int j0 = a; j0 < b; j0 += Ro) {
+                        const int nr = std::min(Ro, b - j0);
+                        const bool ony = !clear(ny, ylohi[0], ylohi[1], j0 - 2, j0 + nr);
+                        kind[onx && ony ? 0 : (ony ? 2 : 1)].push_back(TileTB{i0, i1, j0, nr});
+                    }
+                };
+                if (q < nlo || q >= nmid) {
+                    band(0, ny);
+                } else {
+                    band(0, ya);
+                    band(yb, ny);
+                }
+            }
+            for (int e = 0; e < 8; ++e)
+                for (int g = 1; g <= 2; ++g) {
+                    const size_t n = kind[g].size(), a = n * e / 8, b = n * (e + 1) / 8;
+                    part[(size_t)e].insert(part[(size_t)e].end(), kind[g].begin() + (long)a, kind[g].begin() + (long)b);
+                }
+        };
+        // Chunk length when none is given: the one (4 .. 16 planes) with the
+        // smallest modelled finish time, one workgroup per CU and a tile
+        // costing its planes plus six (those recomputed at its start, and the
+        // first loads).  us per step with 16 planes and with the chunk taken:
+        // 384^3 553, 545 (13), 300^3 375, 347 (11), 210x220x212 167, 124 (4:
+        // all tiles at once, a third as long), 240x200x400 244, 227 (12).
+        int TXo = txo > 0 ? txo : 16;
+        if (txo <= 0) {
+            double bt = 1e300;
+            for (int t = 16; t >= 4; --t) {
+                lay(t);
+                double mk = 0;
+                for (int e = 0; e < 8; ++e) {
+                    std::priority_queue<double, std::vector<double>, std::greater<double>> q;
+                    for (int u = 0; u < std::max(1, cus / 8); ++u) q.push(0.0);
+                    auto tile = [&](const TileTB &x) {
+                        const double f = q.top() + x.i1 - x.i0 + 6;
+                        q.pop();
+                        q.push(f);
+                        mk = std::max(mk, f);
+                    };
+                    for (size_t k = (size_t)e; k < kind[0].size(); k += 8) tile(kind[0][k]);  // (run beside)
+                    for (const TileTB &x : part[(size_t)e]) tile(x);
+                }
+                if (mk < 0.97 * bt) {
+                    bt = mk;
+                    TXo = t;
+                }
+            }
+        }
+        lay(TXo);
+        for (const auto &k : kind)
+            for (const TileTB &x : k) {
+                int64_t xs = 0, ysn = 0;
+                for (int i = x.i0; i < x.i1; ++i) xs += inslab(nx, xlohi[0], xlohi[1], i);
+                for (int jj = x.j0; jj < x.j0 + x.nrows; ++jj) ysn += inslab(ny, ylohi[0], ylohi[1], jj);
+                const int64_t xn = x.i1 - x.i0, nr = x.nrows;
+                pl.tbo_cells += xn * nr * nz;
+                pl.tbo_psi += 4 * (xs * nr * nz + xn * ysn * nz + xn * nr * zs);
+            }
         while (kind[0].size() % 8) kind[0].push_back(TileTB{0, 0, 0, 0});
         pl.tbo = kind[0];
         pl.tbo_n[0] = (int)kind[0].size();
-        std::vector<std::vector<TileTB>> part(8);
         size_t Lp = 0;
-        for (int e = 0; e < 8; ++e) {
-            for (int g = 1; g <= 2; ++g) {
-                const size_t n = kind[g].size(), a = n * e / 8, b = n * (e + 1) / 8;
-                part[(size_t)e].insert(part[(size_t)e].end(), kind[g].begin() + (long)a, kind[g].begin() + (long)b);
-            }
-            Lp = std::max(Lp, part[(size_t)e].size());
-        }
+        for (const auto &q : part) Lp = std::max(Lp, q.size());
         for (auto &q : part) {
             q.resize(Lp, TileTB{0, 0, 0, 0});
             pl.tbo.insert(pl.tbo.end(), q.begin(), q.end());
