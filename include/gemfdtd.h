@@ -446,7 +446,9 @@ int fdtd_batch_cells(const fdtd_batch *b, int64_t *cells);
  * forward pass keeps the last segment's design-cell values).  Device
  * memory: the checkpoints plus 8 B per design cell and step of one
  * segment; ckpt_interval >= T runs no recompute and holds the values of
- * all T steps.
+ * all T steps; with ckpt_interval <= 0 the last segment is lengthened as
+ * far as checkpoints and values take at most twice the memory of
+ * ceil(sqrt T) segments (only that memory if there is not more).
  * loss_out (host, may be NULL); grad_dev: device float32
  * [(i1-i0)*(j1-j0)], written.  On return the handle holds the forward state
  * after T steps and the probe record of the forward run.  FDTD_EINVAL

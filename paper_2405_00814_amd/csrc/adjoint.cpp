@@ -41,15 +41,18 @@ struct StreamSwap {
 }  // namespace
 
 static void copy_state(Sim &s, int set, float *buf, bool to_buf) {
+    CopyParts c{};
     int64_t off = 0;
     auto mv = [&](float *p, int64_t n) {
         if (!p || n <= 0) return;
-        if (to_buf) hip_check(hipMemcpyAsync(buf + off, p, n * 4, hipMemcpyDeviceToDevice, s.st), "ckpt");
-        else hip_check(hipMemcpyAsync(p, buf + off, n * 4, hipMemcpyDeviceToDevice, s.st), "ckpt");
+        c.src[c.count] = to_buf ? p : buf + off;
+        c.dst[c.count] = to_buf ? buf + off : p;
+        c.n[c.count++] = n;
         off += n;
     };
-    for (int c : {FDTD_EZ, FDTD_HX, FDTD_HY}) mv(s.f[set][c], s.ncell);
+    for (int f : {FDTD_EZ, FDTD_HX, FDTD_HY}) mv(s.f[set][f], s.ncell);
     for (int a = 0; a < 4; ++a) mv(s.psi[set][a], s.psi_len[a]);
+    hip_check(launch_copy_parts(c, s.st), "state copy");
 }
 
 static int64_t state_floats(const Sim &s) {
@@ -82,9 +85,11 @@ extern "C" int fdtd_adjoint(fdtd_sim *sim, int64_t T, int64_t n0, int64_t n1, co
                               nullptr);
 }
 
-extern "C" int fdtd_adjoint_grads(fdtd_sim *sim, int64_t T, int64_t n0, int64_t n1, const int32_t *design,
-                                  int32_t ckpt_interval, double *loss_out, float *grad_eps_dev,
-                                  float *grad_sigma_dev, float *grad_mu_dev) {
+// lean: no more memory than checkpoints every L steps take; else up to twice
+// that, and longer: whether more than that was asked for.
+static int adjoint_run(fdtd_sim *sim, int64_t T, int64_t n0, int64_t n1, const int32_t *design, int32_t ckpt_interval,
+                       double *loss_out, float *grad_eps_dev, float *grad_sigma_dev, float *grad_mu_dev, bool lean,
+                       bool &longer) {
     std::vector<void *> tmp;
     Sim *sp = nullptr;
     fdtd_kernel_config saved{};
@@ -120,13 +125,31 @@ extern "C" int fdtd_adjoint_grads(fdtd_sim *sim, int64_t T, int64_t n0, int64_t 
         // an interval beyond T is one segment of T steps
         const int64_t L = std::min<int64_t>(T, ckpt_interval > 0 ? ckpt_interval
                                                                  : (int64_t)std::ceil(std::sqrt((double)T)));
-        const int64_t nseg = (T + L - 1) / L;
+        int64_t nseg = (T + L - 1) / L;
         const int64_t nd = (int64_t)(i1 - i0) * (j1 - j0);
         // captured box: the design box and one row and column beyond it
         // (clipped to the grid), whose Ez the H brackets need
         const int i1c = std::min(i1 + 1, s.nx), j1c = std::min(j1 + 1, s.ny);
         const int64_t ndc = (int64_t)(i1c - i0) * (j1c - j0);
         const int64_t P = (int64_t)s.probe_cells.size();
+        const int64_t S = state_floats(s);
+        // Segments are [g L, (g + 1) L), the last one up to T.  With the
+        // interval left open, the last segment takes as many steps as its
+        // design values fit twice the memory that checkpoints for every L
+        // steps would take (lean: once): its steps are neither checkpointed
+        // nor run again (1024^2, T 1000, a 256^2 box: 13.9 ms with 32 steps
+        // a segment, 11.9 with all values kept, 530 MB for 440).
+        if (ckpt_interval <= 0) {
+            const int64_t once = (nseg - 1) * S + (nseg >= 2 ? 4 : 2) * L * ndc;
+            for (int64_t m = 0; m < nseg - 1; ++m) {  // checkpoints
+                const int64_t need = m * S + 2 * (T - m * L) * ndc + (m > 0 ? 2 * L * ndc : 0);
+                if (need > (lean ? once : 2 * once)) continue;
+                nseg = m + 1;
+                longer = need > once;
+                break;
+            }
+        }
+        auto seg_end = [&](int64_t g) { return g + 1 < nseg ? (g + 1) * L : T; };
 
         // forward and recompute: the chosen fused configuration (variant 2
         // or 3; else the grid's default), the recompute capturing the design
@@ -156,15 +179,15 @@ extern "C" int fdtd_adjoint_grads(fdtd_sim *sim, int64_t T, int64_t n0, int64_t 
             tmp.push_back(p);
             return p;
         };
-        const int64_t S = state_floats(s);
         float *ck = (float *)get((size_t)(std::max<int64_t>(1, nseg - 1) * S) * 4);
-        float *fin = (float *)get((size_t)S * 4);
+        float *fin = nseg >= 2 ? (float *)get((size_t)S * 4) : nullptr;  // (a recompute overwrites the state)
         // design values of a segment, two sets when segments are recomputed
         // (one filled while the adjoint steps read the other)
         float *cap_ez[2] = {nullptr, nullptr}, *cap_br[2] = {nullptr, nullptr};
         for (int b = 0; b < (nseg >= 2 ? 2 : 1); ++b) {
-            cap_ez[b] = (float *)get((size_t)(L * ndc) * 4);
-            cap_br[b] = (float *)get((size_t)(L * ndc) * 4);
+            const int64_t n = b == (int)((nseg - 1) & 1) ? std::max(L, T - (nseg - 1) * L) : L;
+            cap_ez[b] = (float *)get((size_t)(n * ndc) * 4);
+            cap_br[b] = (float *)get((size_t)(n * ndc) * 4);
         }
         const int dbox[4] = {i0, i1, j0, j1};
         const int cbox[4] = {i0, i1c, j0, j1c};
@@ -207,7 +230,7 @@ extern "C" int fdtd_adjoint_grads(fdtd_sim *sim, int64_t T, int64_t n0, int64_t 
         hip_check(hipEventRecord(s.ev0, s.st), "event");
         // ---- forward: checkpoints, then the last segment with its design values ----
         for (int64_t g = 0; g < nseg; ++g) {
-            const int64_t k0 = g * L, k1 = std::min(T, (g + 1) * L);
+            const int64_t k0 = g * L, k1 = seg_end(g);
             if (g + 1 < nseg) {
                 copy_state(s, s.cur, ck + g * S, true);
                 run(k0, k1, nullptr);
@@ -217,7 +240,7 @@ extern "C" int fdtd_adjoint_grads(fdtd_sim *sim, int64_t T, int64_t n0, int64_t 
                 run(k0, k1, &cap);
             }
         }
-        copy_state(s, s.cur, fin, true);
+        if (fin) copy_state(s, s.cur, fin, true);
         // ---- loss ----
         std::vector<float> rec((size_t)(P * T));
         s.records_to_host(rec.data(), T, T);
@@ -376,7 +399,7 @@ extern "C" int fdtd_adjoint_grads(fdtd_sim *sim, int64_t T, int64_t n0, int64_t 
             hip_check(hipStreamWaitEvent(rs, ev_start, 0), "stream wait");
         }
         auto recompute = [&](int64_t g) {
-            const int64_t k0 = g * L, k1 = std::min(T, (g + 1) * L);
+            const int64_t k0 = g * L, k1 = seg_end(g);
             const int b = (int)(g & 1);
             // set b was last read by the adjoint steps of segment g + 2 (the
             // last segment's values come from the forward, in set b too)
@@ -391,7 +414,7 @@ extern "C" int fdtd_adjoint_grads(fdtd_sim *sim, int64_t T, int64_t n0, int64_t 
             hip_check(hipEventRecord(ev_rec[b], rs), "event");
         };
         for (int64_t g = nseg - 1; g >= 0; --g) {
-            const int64_t k0 = g * L, k1 = std::min(T, (g + 1) * L);
+            const int64_t k0 = g * L, k1 = seg_end(g);
             const int b = (int)(g & 1);
             if (g >= 1) recompute(g - 1);
             if (g + 1 < nseg) hip_check(hipStreamWaitEvent(st0, ev_rec[b], 0), "stream wait");
@@ -456,8 +479,10 @@ extern "C" int fdtd_adjoint_grads(fdtd_sim *sim, int64_t T, int64_t n0, int64_t 
             hip_check(launch_grad_combine(shx, shy, dcoef + 4 * nd, dcoef + 5 * nd, grad_mu_dev, nd, s.st),
                       "gradient");
         // leave the forward state after T steps
-        copy_state(s, 0, fin, false);
-        s.cur = 0;
+        if (fin) {
+            copy_state(s, 0, fin, false);
+            s.cur = 0;
+        }
         s.n_done = T;
         s.n_rec = T;
         hip_check(hipEventRecord(s.ev1, s.st), "event");
@@ -485,4 +510,15 @@ extern "C" int fdtd_adjoint_grads(fdtd_sim *sim, int64_t T, int64_t n0, int64_t 
         }
         return rc;
     }
+}
+
+extern "C" int fdtd_adjoint_grads(fdtd_sim *sim, int64_t T, int64_t n0, int64_t n1, const int32_t *design,
+                                  int32_t ckpt_interval, double *loss_out, float *grad_eps_dev,
+                                  float *grad_sigma_dev, float *grad_mu_dev) {
+    bool longer = false, no = false;
+    const int r = adjoint_run(sim, T, n0, n1, design, ckpt_interval, loss_out, grad_eps_dev, grad_sigma_dev,
+                              grad_mu_dev, false, longer);
+    if (r != FDTD_ENOMEM || !longer) return r;
+    return adjoint_run(sim, T, n0, n1, design, ckpt_interval, loss_out, grad_eps_dev, grad_sigma_dev, grad_mu_dev,
+                       true, no);
 }

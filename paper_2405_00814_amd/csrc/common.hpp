@@ -410,6 +410,14 @@ hipError_t launch_advance(int64_t *step_base, int64_t by, hipStream_t st);
 struct Adj2D {
     float *ez, *hx, *hy, *psi_hx, *psi_hy, *psi_ezx, *psi_ezy;
 };
+// dst[q][0 .. n[q]) = src[q][..] for q < count (not overlapping)
+struct CopyParts {
+    const float *src[8];
+    float *dst[8];
+    int64_t n[8];
+    int count;
+};
+hipError_t launch_copy_parts(const CopyParts &c, hipStream_t st);
 // out = dca sez + dcb sbr (the gradient with respect to the parameter whose
 // Ca and Cb derivatives are dca, dcb), rounded to float
 hipError_t launch_grad_combine(const double *sez, const double *sbr, const double *dca, const double *dcb, float *out,
