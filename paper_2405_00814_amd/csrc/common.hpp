@@ -410,6 +410,9 @@ hipError_t launch_advance(int64_t *step_base, int64_t by, hipStream_t st);
 struct Adj2D {
     float *ez, *hx, *hy, *psi_hx, *psi_hy, *psi_ezx, *psi_ezy;
 };
+// In place, in double and rounded once: cb (eps_r if `eps`, else eps_r = 1)
+// -> Cb, ca (null, or sigma) -> Ca, db (null, or mu_r) -> Db.
+hipError_t launch_fold(float *cb, float *ca, float *db, bool eps, int64_t n, double dt, hipStream_t st);
 // dst[q][0 .. n[q]) = src[q][..] for q < count (not overlapping)
 struct CopyParts {
     const float *src[8];

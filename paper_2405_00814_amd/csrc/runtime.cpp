@@ -182,12 +182,19 @@ AxisDev upload_axis(DevAlloc &al, const AxisHost &h, hipStream_t st) {
     a.n = h.n;
     a.lo = h.lo;
     a.hi = h.hi;
-    a.kE = dev_upload(al, h.kE.data(), h.n, st);
-    a.bE = dev_upload(al, h.bE.data(), h.n, st);
-    a.cE = dev_upload(al, h.cE.data(), h.n, st);
-    a.kH = dev_upload(al, h.kH.data(), h.n, st);
-    a.bH = dev_upload(al, h.bH.data(), h.n, st);
-    a.cH = dev_upload(al, h.cH.data(), h.n, st);
+    // the six tables in one block, each at a multiple of 256 bytes
+    const size_t n = ((size_t)h.n + 63) / 64 * 64;
+    std::vector<float> t(6 * n, 0.f);
+    int q = 0;
+    for (const auto *v : {&h.kE, &h.bE, &h.cE, &h.kH, &h.bH, &h.cH})
+        std::copy(v->begin(), v->begin() + h.n, t.begin() + (long)(n * (size_t)q++));
+    float *d = dev_upload(al, t.data(), t.size(), st);
+    a.kE = d;
+    a.bE = d + n;
+    a.cE = d + 2 * n;
+    a.kH = d + 3 * n;
+    a.bH = d + 4 * n;
+    a.cH = d + 5 * n;
     return a;
 }
 
@@ -948,34 +955,21 @@ void Sim::zero_state() {
     n_rec = 0;
 }
 
-// Fold eps_r, sigma, mu_r into Ca, Cb, Db (double, rounded once) and upload.
+// Fold eps_r, sigma, mu_r into Ca, Cb, Db (double, rounded once): the maps
+// are uploaded into the coefficient arrays and folded there.
 void Sim::refold(int64_t c0, int64_t c1) {
     (void)c0;
     (void)c1;
-    std::vector<float> hcb((size_t)ncell), hca, hdb;
-    if (lossy) hca.resize((size_t)ncell);
-    for (int64_t c = 0; c < ncell; ++c) {
-        const double er = eps_r.empty() ? 1.0 : eps_r[(size_t)c];
-        const double sg = sigma.empty() ? 0.0 : sigma[(size_t)c];
-        const double eps = kEps0 * er;
-        const double sh = sg * dt / (2.0 * eps);
-        hcb[(size_t)c] = (float)((dt / eps) / (1.0 + sh));
-        if (lossy) hca[(size_t)c] = (float)((1.0 - sh) / (1.0 + sh));
-    }
-    if (!cb) cb = (float *)al.get((size_t)ncell * 4);
-    hip_check(hipMemcpyAsync(cb, hcb.data(), (size_t)ncell * 4, hipMemcpyHostToDevice, st), "cb");
-    if (lossy) {
-        if (!ca) ca = (float *)al.get((size_t)ncell * 4);
-        hip_check(hipMemcpyAsync(ca, hca.data(), (size_t)ncell * 4, hipMemcpyHostToDevice, st), "ca");
-    }
+    const size_t bytes = (size_t)ncell * 4;
+    if (!cb) cb = (float *)al.get(bytes);
+    if (lossy && !ca) ca = (float *)al.get(bytes);
+    if (mumap && !db) db = (float *)al.get(bytes);
+    if (!eps_r.empty()) hip_check(hipMemcpyAsync(cb, eps_r.data(), bytes, hipMemcpyHostToDevice, st), "cb");
+    if (lossy) hip_check(hipMemcpyAsync(ca, sigma.data(), bytes, hipMemcpyHostToDevice, st), "ca");
+    if (mumap) hip_check(hipMemcpyAsync(db, mu_r.data(), bytes, hipMemcpyHostToDevice, st), "db");
+    hip_check(launch_fold(cb, lossy ? ca : nullptr, mumap ? db : nullptr, !eps_r.empty(), ncell, dt, st), "fold");
     db0 = (float)(dt / (kMu0 * (mu_r.empty() ? 1.0 : mu_r[0])));
-    if (mumap) {
-        hdb.resize((size_t)ncell);
-        for (int64_t c = 0; c < ncell; ++c) hdb[(size_t)c] = (float)(dt / (kMu0 * mu_r[(size_t)c]));
-        if (!db) db = (float *)al.get((size_t)ncell * 4);
-        hip_check(hipMemcpyAsync(db, hdb.data(), (size_t)ncell * 4, hipMemcpyHostToDevice, st), "db");
-    }
-    // the host vectors must live until the copies finish
+    // the host maps may change after the call
     hip_check(hipStreamSynchronize(st), "sync");
 }
 
