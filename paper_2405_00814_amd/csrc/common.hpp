@@ -330,7 +330,7 @@ hipError_t launch_nonfinite(const float *a, int64_t n, int *flag, hipStream_t st
 // sum_k row_k[c] re[k][q] to acc[2q][c] and sum_k row_k[c] im[k][q] to
 // acc[2q+1][c] (nf <= kDftMaxFreq frequencies, acc rows of npts doubles).
 constexpr int kDftMaxFreq = 16;
-constexpr int kDftBatch = 8;
+constexpr int kDftBatch = 14;  // (the phases stay within the 4 KB of a launch's arguments)
 struct DftPhases {
     double re[kDftBatch][kDftMaxFreq], im[kDftBatch][kDftMaxFreq];
 };

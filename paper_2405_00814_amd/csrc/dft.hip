@@ -2,10 +2,10 @@
 // component at a box of cells, fed after every step (the paper motivates
 // frequency-domain responses, Sec. I, without a formulation).  The FP64 sums
 // cost 16 B of reads and writes per frequency and update, so the samples of
-// kDftBatch steps are first gathered into a ring (8 B per cell and step:
+// 8 to kDftBatch steps are first gathered into a ring (8 B per cell and step:
 // one read, one write) and the sums updated once per batch with the
 // buffered steps' phase factors, passed by value: per cell and step about
-// 4 + 32 nf / kDftBatch bytes instead of 4 + 32 nf.  One thread per cell.
+// 4 + 32 nf / 8 bytes instead of 4 + 32 nf.  One thread per cell.
 #include "common.hpp"
 
 namespace gem {
@@ -25,22 +25,26 @@ __global__ __launch_bounds__(256) void k_dft_gather(const float *__restrict__ f,
     row[c] = f[g];
 }
 
+// NB: the most steps buffered
+template <int NB>
 __global__ __launch_bounds__(256) void k_dft_flush(const float *__restrict__ ring, int64_t npts, int nk, int nf,
                                                    DftPhases ph, double *__restrict__ acc) {
     const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= npts) return;
-    double v[kDftBatch];
+    double v[NB];  // (0 beyond nk; phases there are finite)
 #pragma unroll
-    for (int k = 0; k < kDftBatch; ++k) v[k] = k < nk ? (double)ring[k * npts + c] : 0.0;
+    for (int k = 0; k < NB; ++k) v[k] = k < nk ? (double)ring[k * npts + c] : 0.0;
     for (int q = 0; q < nf; ++q) {
-        double re = 0.0, im = 0.0;
+        // step by step onto the sums: the same bits however the steps are
+        // buffered
+        double re = acc[(2 * q) * npts + c], im = acc[(2 * q + 1) * npts + c];
 #pragma unroll
-        for (int k = 0; k < kDftBatch; ++k) {
-            re += v[k] * ph.re[k][q];
-            im += v[k] * ph.im[k][q];
+        for (int k = 0; k < NB; ++k) {
+            re = __builtin_fma(v[k], ph.re[k][q], re);
+            im = __builtin_fma(v[k], ph.im[k][q], im);
         }
-        acc[(2 * q) * npts + c] += re;
-        acc[(2 * q + 1) * npts + c] += im;
+        acc[(2 * q) * npts + c] = re;
+        acc[(2 * q + 1) * npts + c] = im;
     }
 }
 
@@ -56,8 +60,9 @@ hipError_t launch_dft_flush(const float *ring, int64_t npts, int nk, int nf, con
                             hipStream_t st) {
     if (npts <= 0 || nk == 0) return hipSuccess;
     if (nf < 1 || nf > kDftMaxFreq || nk < 0 || nk > kDftBatch) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_dft_flush, dim3((unsigned)((npts + 255) / 256)), dim3(256), 0, st, ring, npts, nk, nf, ph,
-                       acc);
+    const dim3 grid((unsigned)((npts + 255) / 256));
+    if (nk <= 8) hipLaunchKernelGGL((k_dft_flush<8>), grid, dim3(256), 0, st, ring, npts, nk, nf, ph, acc);
+    else hipLaunchKernelGGL((k_dft_flush<kDftBatch>), grid, dim3(256), 0, st, ring, npts, nk, nf, ph, acc);
     return hipGetLastError();
 }
 

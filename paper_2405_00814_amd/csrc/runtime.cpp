@@ -658,7 +658,7 @@ void Sim::dft_accumulate(int64_t step) {
     const DftBox box{dft.box[0], dft.box[2], dft.box[4], dft.box[3] - dft.box[2], dft.box[5] - dft.box[4], ny, nz};
     hip_check(launch_dft_gather(fld, dft.idx, box, dft.npts, dft.ring + (int64_t)r * dft.npts, st), "dft");
     last_launches += 1;
-    if (dft.nbuf == kDftBatch) {
+    if (dft.nbuf >= dft_batch()) {
         dft_flush();
         last_launches += 1;
     }
@@ -874,11 +874,12 @@ void Sim::advance(int64_t n) {
         const int64_t left = n - q, TB = wg_most(), np = (left + TB - 1) / TB;
         int k = (int)((left + np - 1) / np);
         if (mon) {
-            k = std::min(k, kDftBatch - dft.nbuf);
+            if (dft.nbuf >= dft_batch()) dft_flush();  // (filled under another configuration)
+            k = (int)std::min<int64_t>({left, TB, dft_batch() - dft.nbuf});
             const TapArgs tap{dft.comp, dft.box[0], dft.box[1], dft.box[2], dft.box[3], dft.npts,
                               dft.ring + (int64_t)dft_rows(n_done, k) * dft.npts};
             launch_wg2d(n_done, k, nullptr, &tap);
-            if (dft.nbuf == kDftBatch) {
+            if (dft.nbuf >= dft_batch()) {
                 dft_flush();
                 last_launches += 1;
             }
@@ -1684,7 +1685,14 @@ int fdtd_set_dft(fdtd_sim *sim, int component, const int32_t *lo, const int32_t 
         d.idx = dev_upload(s.al, idx.data(), idx.size(), s.st);
     }
     d.acc = (double *)s.al.get((size_t)(2 * nf * d.npts) * 8);  // zero-filled
-    d.ring = (float *)s.al.get((size_t)(kDftBatch * d.npts) * 4);
+    if (s.ndim == 2 && !s.is_graph) {  // (a full pass of the workgroup tiles, if there is the memory)
+        try {
+            d.ring = (float *)s.al.get((size_t)(kDftBatch * d.npts) * 4);
+            d.rows = kDftBatch;
+        } catch (const Fail &) {
+        }
+    }
+    if (!d.ring) d.ring = (float *)s.al.get((size_t)(d.rows * d.npts) * 4);
     hip_check(hipStreamSynchronize(s.st), "sync");
     return FDTD_OK;
     GEM_CATCH

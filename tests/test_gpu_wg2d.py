@@ -152,3 +152,23 @@ def test_wg2d_batch_bits():
         assert np.array_equal(b.probe(q), s.probe()), q
         s.close()
     b.close()
+
+
+def test_wg2d_monitor_across_configurations():
+    """A monitor's buffered samples when the kernel changes between calls:
+    the sums of one configuration throughout."""
+    from paper_2405_00814_amd.sim import Sim
+    pb = _problem((150, 210), (8, 8, 8, 8), 0)
+    init, out = _state(pb.shape), []
+    for kernels in (((2,),) * 4, ((3, (64, 0, 15)), (2,), (3, (64, 0, 3)), (3, (64, 1, 14)))):
+        s = Sim.from_problem(pb)
+        for f, a in init.items():
+            s.set_field(f, a)
+        s.set_kernel(*kernels[0])
+        s.set_dft("ez", (3, 5), (149, 200), [1e9, 2.5e9])
+        for k, n in zip(kernels, (27, 6, 5, 40)):
+            s.set_kernel(*k)
+            s.step(n)
+        out.append(s.get_dft()[0])
+        s.close()
+    assert np.array_equal(out[0], out[1])
