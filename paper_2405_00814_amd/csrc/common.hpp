@@ -421,6 +421,14 @@ struct CopyParts {
     int count;
 };
 hipError_t launch_copy_parts(const CopyParts &c, hipStream_t st);
+// p[q][0 .. n[q]) = 0 for q < count
+struct ZeroParts {
+    static constexpr int kMost = 64;
+    float *p[kMost];
+    int64_t n[kMost];
+    int count;
+};
+hipError_t launch_zero_parts(const ZeroParts &z, hipStream_t st);
 // out = dca sez + dcb sbr (the gradient with respect to the parameter whose
 // Ca and Cb derivatives are dca, dcb), rounded to float
 hipError_t launch_grad_combine(const double *sez, const double *sbr, const double *dca, const double *dcb, float *out,

@@ -940,17 +940,23 @@ void Sim::split_check() const {
 }
 
 void Sim::zero_state() {
+    ZeroParts z{};
+    static_assert(3 * (6 + NPSI3) + 3 <= ZeroParts::kMost, "parts of a state");
+    auto add = [&](void *p, int64_t n) {
+        if (!p || n <= 0) return;
+        z.p[z.count] = (float *)p;
+        z.n[z.count++] = n;
+    };
     for (int s = 0; s < 3; ++s) {
-        for (int c = 0; c < 6; ++c)
-            if (f[s][c]) hip_check(hipMemsetAsync(f[s][c], 0, (size_t)ncell * 4, st), "memset");
-        for (int a = 0; a < NPSI3; ++a)
-            if (psi[s][a]) hip_check(hipMemsetAsync(psi[s][a], 0, (size_t)psi_len[a] * 4, st), "memset");
+        for (int c = 0; c < 6; ++c) add(f[s][c], ncell);
+        for (int a = 0; a < NPSI3; ++a) add(psi[s][a], psi_len[a]);
     }
-    if (is_graph && g.x) hip_check(hipMemsetAsync(g.x, 0, (size_t)g.nnodes * 4, st), "memset");
-    if (dft.acc) hip_check(hipMemsetAsync(dft.acc, 0, (size_t)(2 * dft.nf * dft.npts) * 8, st), "memset");
+    if (is_graph) add(g.x, g.nnodes);
+    add(dft.acc, 4LL * dft.nf * dft.npts);
     dft.nacc = 0;
     dft.nbuf = 0;
-    if (ezy) hip_check(hipMemsetAsync(ezy, 0, (size_t)ncell * 4, st), "memset");
+    add(ezy, ncell);
+    hip_check(launch_zero_parts(z, st), "clear state");
     cur = 0;
     n_done = 0;
     n_rec = 0;
