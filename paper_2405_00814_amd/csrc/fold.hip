@@ -31,7 +31,7 @@ hipError_t launch_fold(float *cb, float *ca, float *db, bool eps, int64_t n, dou
 
 // Clears arrays in one launch: a reset, 64 steps and the read-out of a 32^2
 // grid took 127 us with a memset of each array, 100 with this; 250^2, 1024
-// steps 1.37 ms, 1.30.  Bound by the launch, on large grids by the stores.
+// steps 1.37 ms, 1.30.  Bound by the launch.
 __global__ __launch_bounds__(256) void k_zero_parts(ZeroParts z) {
     int64_t b = blockIdx.x;
     int q = 0;
