@@ -117,7 +117,7 @@ __global__ __launch_bounds__(256) void k3d_flat(Prob3D p, Div dplane, Div drow, 
     const float ezCa = Ez[ox - mz], ezCb = Ez[oy - mz];
     const float cb = p.cb[cc];
     float ca = 1.f, db = p.db0, dbA = db, dbB = db, dbC = db;
-    if (MAT >= 1) ca = p.ca[cc];
+    if (MAT == 1 || (MAT == 2 && p.ca)) ca = p.ca[cc];  // (a Db map may come without a Ca map)
     if (MAT == 2) { db = p.db[cc]; dbA = p.db[cc - mx]; dbB = p.db[cc - my]; dbC = p.db[cc - mz]; }
 
     // psi: H of the own cell (w*), of the cells below (A: i-1, B: j-1, C:

@@ -345,7 +345,7 @@ __device__ __forceinline__ void two_tile(const Prob3D &p, const TileTB &T, int t
         ld(cb, p.cb, c, cond);
 #pragma unroll
         for (int v = 0; v < V; ++v) { ca[v] = 1.f; db[v] = p.db0; }
-        if (MAT >= 1 && cond) ldv<V>(ca, p.ca + c);
+        if ((MAT == 1 || (MAT == 2 && p.ca)) && cond) ldv<V>(ca, p.ca + c);  // (a Db map may come without a Ca map)
         if (MAT == 2 && cond) ldv<V>(db, p.db + c);
     };
 

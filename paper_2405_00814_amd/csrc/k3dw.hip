@@ -184,7 +184,7 @@ __global__ __launch_bounds__(64 * WPB) void k3d_march(Prob3D p, const Tile3 *til
         ld(cb, p.cb, c, ok);
 #pragma unroll
         for (int v = 0; v < V; ++v) { ca[v] = 1.f; db[v] = p.db0; }
-        if (MAT >= 1 && ok) ldv<V>(ca, p.ca + c);
+        if ((MAT == 1 || (MAT == 2 && p.ca)) && ok) ldv<V>(ca, p.ca + c);  // (a Db map may come without a Ca map)
         if (MAT == 2 && ok) ldv<V>(db, p.db + c);
         const bool s63 = ok && last && ke;
         const float ey_e = s63 ? ey0[r0 + kend] : 0.f;
