@@ -2008,6 +2008,9 @@ int fdtd_set_material(fdtd_sim *sim, const int32_t *lo, const int32_t *hi, const
             }
     }
     hip_check(hipStreamSynchronize(s.st), "sync");
+    // memory first: a failure leaves the maps and the kernels' choice alone
+    const bool lossy = s.lossy || (sigma && std::any_of(sigma, sigma + bn, [](float v) { return v > 0.f; }));
+    if (lossy && !s.ca) s.ca = (float *)s.al.get((size_t)s.ncell * 4);
     if (s.eps_r.empty()) s.eps_r.assign((size_t)s.ncell, 1.0f);
     if (sigma && s.sigma.empty()) s.sigma.assign((size_t)s.ncell, 0.0f);
     int64_t q = 0;
@@ -2018,8 +2021,7 @@ int fdtd_set_material(fdtd_sim *sim, const int32_t *lo, const int32_t *hi, const
                 s.eps_r[(size_t)c] = eps_r[q];
                 if (sigma) s.sigma[(size_t)c] = sigma[q];
             }
-    if (sigma && !s.lossy)
-        s.lossy = std::any_of(s.sigma.begin(), s.sigma.end(), [](float v) { return v > 0.f; });
+    s.lossy = lossy;
     s.refold(0, s.ncell);
     if (s.is_graph) graph_refold(s);
     return FDTD_OK;

@@ -1,0 +1,93 @@
+"""Calls on a live handle whose allocations fail (a caller's allocator that
+returns NULL from the k-th call on): they return FDTD_ENOMEM, and the handle
+steps on as if the call had not been made."""
+import ctypes as C
+
+import numpy as np
+import pytest
+
+from paper_2405_00814_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture
+def budget(monkeypatch):
+    """Allocations left to the library; None: no limit."""
+    import torch
+    from paper_2405_00814_amd import _lib as L
+    from paper_2405_00814_amd import sim
+    left = {"n": None}
+
+    def alloc(ctx, size, stream):
+        if left["n"] is not None:
+            if left["n"] <= 0:
+                return None
+            left["n"] -= 1
+        return int(torch.cuda.caching_allocator_alloc(int(size), stream=int(stream or 0)))
+
+    def free(ctx, ptr, stream):
+        torch.cuda.caching_allocator_delete(int(ptr))
+
+    cb = L.ALLOC_FN(alloc), L.FREE_FN(free)
+    a = L.fdtd_allocator(None, *cb)
+    monkeypatch.setattr(sim, "torch_allocator", lambda: a)
+    yield left
+    left["n"] = None
+
+
+def _fails_until_it_fits(left, call):
+    """call() with room for 0, 1, ... allocations: FDTD_ENOMEM until it fits;
+    yields after each failure with the limit lifted."""
+    from paper_2405_00814_amd import _lib as L
+    for k in range(60):
+        left["n"] = k
+        try:
+            call()
+        except L.FdtdError as e:
+            assert e.code == L.FDTD_ENOMEM, e
+            left["n"] = None
+            yield k
+            continue
+        left["n"] = None
+        return
+    raise AssertionError("never fitted")
+
+
+def _problem(ndim):
+    if ndim == 2:
+        return W.dielectric2d(96, ny=80, steps=40, seed=2, nrect=3, side=(6, 20), npml=8, nprobes=2)
+    return W.yee3d(shape=(20, 22, 24), steps=40, seed=2, nbox=3, side=(3, 8), npml=4, nprobes=2, tau_steps=6.0)
+
+
+def _state(s, fields):
+    return [s.get_field(f) for f in fields] + [s.probe()]
+
+
+@pytest.mark.parametrize("ndim", [2, 3])
+def test_set_material_adding_loss(budget, ndim):
+    """A box that makes a lossless grid lossy needs a Ca map."""
+    from paper_2405_00814_amd.sim import Sim
+    pb = _problem(ndim)
+    pb.sigma = None
+    fields = ("ez", "hx", "hy") if ndim == 2 else ("ex", "ey", "ez", "hx", "hy", "hz")
+    lo, hi = (10,) * ndim, (16,) * ndim
+    eps, sig = np.full((6,) * ndim, 2, np.float32), np.full((6,) * ndim, 0.02, np.float32)
+    a, b = Sim.from_problem(pb), Sim.from_problem(pb)
+    failed = 0
+    a.step(20)
+    b.step(20)
+    for k in _fails_until_it_fits(budget, lambda: a.set_material(lo, hi, eps, sig)):
+        failed += 1
+        a.step(5)
+        b.step(5)
+        for u, v in zip(_state(a, fields), _state(b, fields)):
+            assert np.array_equal(u, v), k
+    assert failed
+    b.set_material(lo, hi, eps, sig)
+    for s in (a, b):
+        s.step(15)
+    for u, v in zip(_state(a, fields), _state(b, fields)):
+        assert np.array_equal(u, v)
+    a.close()
+    b.close()
