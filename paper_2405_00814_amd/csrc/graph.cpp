@@ -313,6 +313,7 @@ static void build_graph_split(Sim &s) {
     }
     Sim::Graph &g = s.g;
     g.bytes = 0;
+    g.layers_ok = false;
     put_layer(s, g.h, hm, nullptr);
     put_layer(s, g.e, em, nullptr);
     g.nmain = nnodes;
@@ -339,6 +340,7 @@ static void build_graph_split(Sim &s) {
     s.al.put(s.ezy);
     s.ezy = nullptr;
     hip_check(hipStreamSynchronize(s.st), "sync");
+    g.layers_ok = true;
 }
 
 // Nonzeros of the largest layer of the explicit graph of an nx x ny grid
@@ -480,6 +482,7 @@ void build_graph(Sim &s) {
 
     Sim::Graph &g = s.g;
     g.bytes = 0;
+    g.layers_ok = false;
     put_layer(s, g.h, hm, &ha);
     put_layer(s, g.e, em, &ea);
     g.nmain = nmain;
@@ -501,50 +504,27 @@ void build_graph(Sim &s) {
         }
     }
     hip_check(hipStreamSynchronize(s.st), "sync");
+    g.layers_ok = true;
 }
 
 void graph_refold(Sim &s) {
+    s.g.lists_ok = false;  // (they name runs of the E layer)
     build_graph(s);
     graph_set_source_probes(s);
 }
 
-void graph_set_source_probes(Sim &s) {
+void graph_ensure(Sim &s) {
+    if (!s.g.layers_ok) graph_refold(s);
+    else if (!s.g.lists_ok) graph_set_source_probes(s);
+}
+
+// The source and the probes by the run of the E layer that holds each node,
+// so that the layer's launch takes them along; false where a node that no
+// row writes (on the low walls) leaves them all to a launch of their own.
+static bool graph_lists_by_run(Sim &s) {
     Sim::Graph &g = s.g;
-    s.al.put(g.src_nodes);
-    g.src_nodes = nullptr;
-    g.nsrc = 0;
-    if (s.src_idx >= 0) {
-        std::vector<int> sn;
-        for (int i = s.src_box[0]; i < s.src_box[1]; ++i)
-            for (int j = s.src_box[2]; j < s.src_box[3]; ++j) sn.push_back((int)g.ez_node[(size_t)i * s.ny + j]);
-        int64_t dummy = 0;
-        g.src_nodes = up(s.al, sn, s.st, dummy);
-        g.nsrc = (int)sn.size();
-        hip_check(hipStreamSynchronize(s.st), "sync");
-    }
-    s.al.put(g.probe_node);
-    s.al.put(g.probe_node2);
-    g.probe_node = g.probe_node2 = nullptr;
-    if (!s.probe_cells.empty()) {
-        std::vector<int> pn(s.probe_cells.size()), pn2(s.probe_cells.size());
-        for (size_t p = 0; p < pn.size(); ++p) pn[p] = (int)g.ez_node[(size_t)s.probe_cells[p]];
-        int64_t dummy = 0;
-        g.probe_node = up(s.al, pn, s.st, dummy);
-        if (!g.ez_node2.empty()) {  // split field: Ez = Ezx + Ezy
-            for (size_t p = 0; p < pn.size(); ++p) pn2[p] = (int)g.ez_node2[(size_t)s.probe_cells[p]];
-            g.probe_node2 = up(s.al, pn2, s.st, dummy);
-        }
-        hip_check(hipStreamSynchronize(s.st), "sync");
-    }
-    // By the run of the E layer that holds each node, so that the layer's
-    // launch takes source and probes along; a node that no row writes (on
-    // the low walls) leaves them all to a launch of their own.
-    for (void *p : {(void *)g.src_mask, (void *)g.probe_start, (void *)g.probe_row, (void *)g.probe_slot}) s.al.put(p);
-    g.src_mask = nullptr;
-    g.probe_start = g.probe_row = g.probe_slot = nullptr;
-    g.in_runs = false;
     const Sim::Graph::Layer &L = g.e;
-    if (!L.rec || !g.ez_node2.empty()) return;
+    if (!L.rec || !g.ez_node2.empty()) return false;
     auto find = [&](int64_t node, int &run, int &row) {
         auto it = std::upper_bound(L.runs.begin(), L.runs.end(), node,
                                    [](int64_t v, const std::array<int, 4> &r) { return v < r[0]; });
@@ -562,13 +542,13 @@ void graph_set_source_probes(Sim &s) {
         mask.assign((size_t)L.nrun, 0);
         for (int i = s.src_box[0]; i < s.src_box[1]; ++i)
             for (int j = s.src_box[2]; j < s.src_box[3]; ++j) {
-                if (!find(g.ez_node[(size_t)i * s.ny + j], run, row)) return;
+                if (!find(g.ez_node[(size_t)i * s.ny + j], run, row)) return false;
                 mask[(size_t)run] |= (uint64_t)1 << row;
             }
     }
     std::vector<std::array<int, 3>> pr;  // {run, row, probe}
     for (size_t p = 0; p < s.probe_cells.size(); ++p) {
-        if (!find(g.ez_node[(size_t)s.probe_cells[p]], run, row)) return;
+        if (!find(g.ez_node[(size_t)s.probe_cells[p]], run, row)) return false;
         pr.push_back({run, row, (int)p});
     }
     std::sort(pr.begin(), pr.end());
@@ -587,7 +567,40 @@ void graph_set_source_probes(Sim &s) {
         g.probe_slot = up(s.al, pslot, s.st, dummy);
     }
     hip_check(hipStreamSynchronize(s.st), "sync");
-    g.in_runs = true;
+    return true;
+}
+
+void graph_set_source_probes(Sim &s) {
+    Sim::Graph &g = s.g;
+    g.lists_ok = g.in_runs = false;
+    for (void *p : {(void *)g.src_nodes, (void *)g.probe_node, (void *)g.probe_node2, (void *)g.src_mask, (void *)g.probe_start,
+                    (void *)g.probe_row, (void *)g.probe_slot})
+        s.al.put(p);
+    g.src_nodes = g.probe_node = g.probe_node2 = g.probe_start = g.probe_row = g.probe_slot = nullptr;
+    g.src_mask = nullptr;
+    g.nsrc = 0;
+    if (s.src_idx >= 0) {
+        std::vector<int> sn;
+        for (int i = s.src_box[0]; i < s.src_box[1]; ++i)
+            for (int j = s.src_box[2]; j < s.src_box[3]; ++j) sn.push_back((int)g.ez_node[(size_t)i * s.ny + j]);
+        int64_t dummy = 0;
+        g.src_nodes = up(s.al, sn, s.st, dummy);
+        g.nsrc = (int)sn.size();
+        hip_check(hipStreamSynchronize(s.st), "sync");
+    }
+    if (!s.probe_cells.empty()) {
+        std::vector<int> pn(s.probe_cells.size()), pn2(s.probe_cells.size());
+        for (size_t p = 0; p < pn.size(); ++p) pn[p] = (int)g.ez_node[(size_t)s.probe_cells[p]];
+        int64_t dummy = 0;
+        g.probe_node = up(s.al, pn, s.st, dummy);
+        if (!g.ez_node2.empty()) {  // split field: Ez = Ezx + Ezy
+            for (size_t p = 0; p < pn.size(); ++p) pn2[p] = (int)g.ez_node2[(size_t)s.probe_cells[p]];
+            g.probe_node2 = up(s.al, pn2, s.st, dummy);
+        }
+        hip_check(hipStreamSynchronize(s.st), "sync");
+    }
+    g.in_runs = graph_lists_by_run(s);
+    g.lists_ok = true;
 }
 
 void graph_step(Sim &s, int64_t step) {

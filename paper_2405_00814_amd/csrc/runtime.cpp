@@ -1507,6 +1507,7 @@ int fdtd_step(fdtd_sim *sim, int64_t n) {
     s.ensure_source(s.n_done + n);
     s.ensure_rec(s.n_rec + n);
     s.build_probe_tiles();
+    if (s.is_graph) graph_ensure(s);
     s.last_launches = 0;
     hip_check(hipEventRecord(s.ev0, s.st), "event");
     s.advance(n);
@@ -1538,6 +1539,7 @@ int fdtd_step_profile(fdtd_sim *sim, int32_t steps, fdtd_launch_stat *out, int32
     s.ensure_source(s.n_done + steps);
     s.ensure_rec(s.n_rec + steps);
     s.build_probe_tiles();
+    if (s.is_graph) graph_ensure(s);
     const bool fused3 = s.ndim == 3 && !s.is_graph && s.kcfg.variant >= 2;
     const bool two = fused3 && s.kcfg.variant == 3 && steps >= 2;
     const bool tb2 = s.ndim == 2 && !s.is_graph && s.kcfg.variant == 3 && steps >= s.kcfg.tile[2];
@@ -2013,17 +2015,33 @@ int fdtd_set_material(fdtd_sim *sim, const int32_t *lo, const int32_t *hi, const
     if (lossy && !s.ca) s.ca = (float *)s.al.get((size_t)s.ncell * 4);
     if (s.eps_r.empty()) s.eps_r.assign((size_t)s.ncell, 1.0f);
     if (sigma && s.sigma.empty()) s.sigma.assign((size_t)s.ncell, 0.0f);
-    int64_t q = 0;
-    for (int i = l[0]; i < h[0]; ++i)
-        for (int j = l[1]; j < h[1]; ++j)
-            for (int k = l[2]; k < h[2]; ++k, ++q) {
-                const int64_t c = ((int64_t)i * s.ny + j) * s.nz + k;
-                s.eps_r[(size_t)c] = eps_r[q];
-                if (sigma) s.sigma[(size_t)c] = sigma[q];
-            }
+    // the box's values into the maps, the former ones into e0 and s0
+    const bool was_lossy = s.lossy;
+    std::vector<float> e0((size_t)bn), s0(sigma ? (size_t)bn : 0);
+    auto put_box = [&](const float *e, const float *g, float *eo, float *go) {
+        int64_t q = 0;
+        for (int i = l[0]; i < h[0]; ++i)
+            for (int j = l[1]; j < h[1]; ++j)
+                for (int k = l[2]; k < h[2]; ++k, ++q) {
+                    const size_t c = (size_t)(((int64_t)i * s.ny + j) * s.nz + k);
+                    if (eo) eo[q] = s.eps_r[c];
+                    s.eps_r[c] = e[q];
+                    if (!g) continue;
+                    if (go) go[q] = s.sigma[c];
+                    s.sigma[c] = g[q];
+                }
+    };
+    put_box(eps_r, sigma, e0.data(), s0.data());
     s.lossy = lossy;
-    s.refold(0, s.ncell);
-    if (s.is_graph) graph_refold(s);
+    try {
+        s.refold(0, s.ncell);
+        if (s.is_graph) graph_refold(s);
+    } catch (...) {  // as it was: the graph is rebuilt by the next stepping call
+        put_box(e0.data(), sigma ? s0.data() : nullptr, nullptr, nullptr);
+        s.lossy = was_lossy;
+        if (s.is_graph) s.g.layers_ok = false;
+        throw;
+    }
     return FDTD_OK;
     GEM_CATCH
 }

@@ -219,6 +219,10 @@ struct Sim {
         uint64_t *src_mask = nullptr;
         int *probe_start = nullptr, *probe_row = nullptr, *probe_slot = nullptr;
         bool in_runs = false;
+        // cleared while a rebuild of the layers, of the source and probe
+        // lists is under way: after one that failed (out of memory), the
+        // next stepping call repeats it
+        bool layers_ok = true, lists_ok = true;
         std::vector<int64_t> ez_node;     // node of Ez(i,j) (host; split field: of Ezx)
         std::vector<int64_t> ez_node2;    // split field: node of Ezy(i,j), else empty
         int *src_nodes = nullptr;  // device: the source box's Ez nodes
@@ -278,6 +282,8 @@ struct Sim {
 void build_graph(Sim &s);
 void graph_step(Sim &s, int64_t step);
 void graph_refold(Sim &s);
+// what a failed rebuild left to do
+void graph_ensure(Sim &s);
 void graph_set_source_probes(Sim &s);
 // node of component comp at cell (i, j) in the graph's node vector
 int64_t graph_node(const Sim &s, int comp, int i, int j);

@@ -91,3 +91,34 @@ def test_set_material_adding_loss(budget, ndim):
         assert np.array_equal(u, v)
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("split", [0, 1])
+@pytest.mark.parametrize("shape", [(96, 80), (40, 36)])  # layers as runs of rows, and by CSR
+def test_graph_set_material(budget, shape, split):
+    """The layers are built again for new material: a rebuild that failed
+    half-way is not stepped on."""
+    from paper_2405_00814_amd.sim import Sim
+    pb = W.dielectric2d(shape[0], ny=shape[1], steps=40, seed=2, nrect=3, side=(4, 12), npml=8, nprobes=2)
+    pb.sigma = None
+    pb.cpml = dict(m=3.0, sigma_max=0.0, kappa_max=1.0, alpha_max=0.0, m_alpha=1.0, split=split)
+    a, b = (Sim.from_problem(pb, graph=True) for _ in range(2))
+    lo, hi = (12, 12), (20, 20)
+    eps, sig = np.full((8, 8), 2, np.float32), np.full((8, 8), 0.02, np.float32)
+    failed = 0
+    for s in (a, b):
+        s.step(20)
+    for k in _fails_until_it_fits(budget, lambda: a.set_material(lo, hi, eps, sig)):
+        failed += 1
+        for s in (a, b):
+            s.step(3)
+        for u, v in zip(_state(a, ("ez", "hx", "hy")), _state(b, ("ez", "hx", "hy"))):
+            assert np.array_equal(u, v), k
+    assert failed > 3
+    b.set_material(lo, hi, eps, sig)
+    for s in (a, b):
+        s.step(15)
+    for u, v in zip(_state(a, ("ez", "hx", "hy")), _state(b, ("ez", "hx", "hy"))):
+        assert np.array_equal(u, v)
+    a.close()
+    b.close()
