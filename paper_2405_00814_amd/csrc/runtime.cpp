@@ -1475,23 +1475,34 @@ int fdtd_set_probes(fdtd_sim *sim, int component, const int32_t *ijk, int32_t n)
         if (cells[(size_t)q] < 0) fail(FDTD_EINVAL, "probe cell outside the grid");
     }
     hip_check(hipStreamSynchronize(s.st), "sync");
+    // the new cells are on the device before the old ones go; the tiles'
+    // and the graph's lists of them are made again by the next stepping call
+    // where that fails below
+    int *dev = nullptr;
+    int64_t *dev64 = nullptr;
+    if (n > 0) {
+        std::vector<int> c32((size_t)n);
+        for (int q = 0; q < n; ++q) c32[(size_t)q] = (int)cells[(size_t)q];
+        dev = dev_upload(s.al, c32.data(), (size_t)n, s.st);
+        try {
+            dev64 = dev_upload(s.al, cells.data(), (size_t)n, s.st);
+        } catch (...) {
+            s.al.put(dev);
+            throw;
+        }
+    }
     s.probe_cells = cells;
     s.probe_comp = component;
     s.al.put(s.probe_dev);
     s.al.put(s.probe_dev64);
     s.al.put(s.rec_dev);
-    s.probe_dev = nullptr;
-    s.probe_dev64 = nullptr;
+    s.probe_dev = dev;
+    s.probe_dev64 = dev64;
     s.rec_dev = nullptr;
     s.rec_cap = 0;
     s.n_rec = 0;
-    if (n > 0) {
-        std::vector<int> c32((size_t)n);
-        for (int q = 0; q < n; ++q) c32[(size_t)q] = (int)cells[(size_t)q];
-        s.probe_dev = dev_upload(s.al, c32.data(), (size_t)n, s.st);
-        s.probe_dev64 = dev_upload(s.al, cells.data(), (size_t)n, s.st);
-    }
     s.pt_ntiles = -1;
+    if (s.is_graph) s.g.lists_ok = s.g.in_runs = false;
     s.build_probe_tiles();
     if (s.is_graph) graph_set_source_probes(s);
     hip_check(hipStreamSynchronize(s.st), "sync");

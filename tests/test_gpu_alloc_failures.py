@@ -122,3 +122,34 @@ def test_graph_set_material(budget, shape, split):
         assert np.array_equal(u, v)
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("form", ["reference", "tiles", "graph", "3d"])
+def test_set_probes(budget, form):
+    """New probes whose lists do not fit: the fields step on, and the call
+    made again records from there."""
+    from paper_2405_00814_amd.sim import Sim
+    pb = _problem(3 if form == "3d" else 2)
+    fields = ("ez", "hx", "hy")
+    a, b = (Sim.from_problem(pb, graph=form == "graph") for _ in range(2))
+    if form == "reference":
+        for s in (a, b):
+            s.set_kernel(1)
+    cells = pb.probes + 1
+    failed = 0
+    for s in (a, b):
+        s.step(20)
+    for k in _fails_until_it_fits(budget, lambda: a.set_probes("ez", cells)):
+        failed += 1
+        for s in (a, b):
+            s.step(3)
+        for f in fields:
+            assert np.array_equal(a.get_field(f), b.get_field(f)), (k, f)
+    assert failed
+    b.set_probes("ez", cells)
+    for s in (a, b):
+        s.step(9)
+    for u, v in zip(_state(a, fields), _state(b, fields)):
+        assert np.array_equal(u, v)
+    a.close()
+    b.close()
