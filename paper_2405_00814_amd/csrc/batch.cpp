@@ -104,34 +104,15 @@ struct BFail {
 
 static void batch_build_probes(fdtd_batch &b) {
     if (b.wg.TB > 0) {
-        // (tile, problem's probe): the tiles of a problem are one range of
-        // the list before the sort by rows, so search by problem
-        std::vector<std::vector<int>> of(b.sims.size());
-        for (size_t t = 0; t < b.wg.list.size(); ++t) of[(size_t)b.wg.list[t].prob].push_back((int)t);
-        std::vector<std::pair<int, std::pair<int, int>>> ent;  // (tile, (cell, slot))
+        std::vector<WgProbe> pr;
         for (size_t q = 0; q < b.sims.size(); ++q) {
             const Sim &s = *b.sims[q];
-            for (size_t p = 0; p < s.probe_cells.size(); ++p) {
-                const int i = (int)(s.probe_cells[p] / s.ny), j = (int)(s.probe_cells[p] % s.ny);
-                for (int t : of[q]) {
-                    const TileW &T = b.wg.list[(size_t)t];
-                    if (i >= T.i0 && i < T.i1 && j >= T.j0 && j < T.j1)
-                        ent.push_back({t, {(int)s.probe_cells[p], (int)p}});
-                }
-            }
+            for (size_t p = 0; p < s.probe_cells.size(); ++p)
+                pr.push_back(WgProbe{(int)q, (int)(s.probe_cells[p] / s.ny), (int)(s.probe_cells[p] % s.ny), (int)p});
         }
-        std::stable_sort(ent.begin(), ent.end(), [](const auto &u, const auto &v) { return u.first < v.first; });
-        std::vector<int> start(b.wg.list.size() + 1, 0), cell(1, 0), slot(1, 0);
-        if (!ent.empty()) {
-            cell.clear();
-            slot.clear();
-        }
-        for (auto &e : ent) {
-            start[(size_t)e.first + 1]++;
-            cell.push_back(e.second.first);
-            slot.push_back(e.second.second);
-        }
-        for (size_t t = 0; t + 1 < start.size(); ++t) start[t + 1] += start[t];
+        std::vector<int> start, cell, slot;
+        wg2d_probes(b.wg.list, 0, pr, start, cell, slot);
+        if (cell.empty()) cell.push_back(0), slot.push_back(0);
         b.al.put(b.wg.pt_start);
         b.al.put(b.wg.pt_cell);
         b.al.put(b.wg.pt_slot);

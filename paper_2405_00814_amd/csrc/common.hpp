@@ -217,6 +217,16 @@ bool wg2d_supported(int ny, int sx, int sy, int cls, int TB);
 // tiles of one problem for passes of at most TB steps, ordered by rows
 void wg2d_plan(int prob, int nx, int ny, int cls, int mat, int TB, const int *xlohi, const int *ylohi,
                std::vector<TileW> &tiles);
+// Probe lists of the tiles (start, cell, slot as ProbeTiles; cell: row << 6 |
+// column in the tile, in increasing order, equal ones by slot); tiles and
+// probes in the order of their problems.  rows = 0:
+// the tile that writes a probe's cell; else every tile that loads it (`rows`
+// rows each).
+struct WgProbe {
+    int prob, i, j, slot;
+};
+void wg2d_probes(const std::vector<TileW> &tiles, int rows, const std::vector<WgProbe> &probes, std::vector<int> &start,
+                 std::vector<int> &cell, std::vector<int> &slot);
 // size class and steps per pass for grids (nx, ny) advanced together on
 // `cus` compute units
 void wg2d_default(const std::vector<std::pair<int, int>> &grids, int mat, int cus, int &cls, int &TB);

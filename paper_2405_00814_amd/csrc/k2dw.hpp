@@ -110,9 +110,28 @@ struct Buf {
     }
 };
 
+// The entries of a tile's probe list (ordered by row) that lie in its rows
+// [r0, r0 + n): the first and their number.
+__device__ __forceinline__ void wave_entries(const ProbeTiles &pt, int tile, int r0, int n, int lane, int &first,
+                                             int &count) {
+    first = count = 0;
+    if (pt.start == nullptr) return;
+    const int b = load_const(pt.start + tile), e = load_const(pt.start + tile + 1);
+    for (int q = b; q < e; q += 64) {
+        const int row = q + lane < e ? pt.cell[q + lane] >> 6 : -1;
+        const uint64_t m = __ballot(row >= r0 && row < r0 + n);
+        if (m == 0) continue;
+        if (count == 0) first = q + __builtin_ctzll(m);
+        count += __popcll(m);
+    }
+    first = __builtin_amdgcn_readfirstlane(first);
+    count = __builtin_amdgcn_readfirstlane(count);
+}
+
 template <int W, int RP>
 struct WgShared {
     float e[2][W][2][64];        // Ez of each wavefront's first and last row
+    int2 pr[W][64];              // each wavefront's first 64 probes: {row << 6 | column, slot}
     RowTab x[W * RP + 1];        // x-axis tables (CPML tiles); entry 0: row a - 1
 };
 
@@ -240,33 +259,52 @@ __device__ __forceinline__ void wg_tile(const Prob2D &p, const TileW &T, const W
     auto src_at = [&](int64_t n) { return srcw && n < p.src_len ? load_const(p.src_vals + n) : 0.f; };
     float sval = src_at(step);
 
-    // probes of the tile held by this wavefront: the first two cached, the
-    // others looked up at every step
-    const int pbeg = A.pt.start != nullptr ? load_const(A.pt.start + tile) : 0,
-              pend = A.pt.start != nullptr ? load_const(A.pt.start + tile + 1) : 0;
-    int np = 0, pr0 = 0, pl0 = -1, ps0 = 0, pr1 = 0, pl1 = -1, ps1 = 0, prest = pend;
-    for (int q = pbeg; q < pend; ++q) {
-        const int cell = load_const(A.pt.cell + q), pi = cell / ny, pj = cell - pi * ny;
-        if (pi < ib || pi >= ib + R) continue;
-        if (np == 0) { pr0 = pi - ib; pl0 = pj - T.c; ps0 = load_const(A.pt.slot + q); }
-        else if (np == 1) { pr1 = pi - ib; pl1 = pj - T.c; ps1 = load_const(A.pt.slot + q); }
-        else if (np == 2) prest = q;
-        ++np;
+    // probes in this wavefront's rows, one per lane: the first 64, and the
+    // rows that hold them, in registers where the rows leave some (4 rows:
+    // 128^2 with four probes 0.79 us per step, 0.87 without), else in LDS;
+    // further ones read again at every step.  A lane's value comes from the
+    // lane of its column, row by row over the rows that hold probes (looked
+    // up one by one, behind scalar loads, 64 probes on a 64^2 grid took 16 us
+    // per step, 0.88 so)
+    constexpr bool KEEP = R <= 4;
+    int2 mine = make_int2(0, 0);
+    int pfirst, pcount;
+    wave_entries(A.pt, tile, w * R, R, lane, pfirst, pcount);
+    if (pcount > 0) {  // (uniform: the wait for these loads is a wait for all before them)
+        const int q = pfirst + min(lane, pcount - 1);
+        mine = make_int2(A.pt.cell[q] - (w * R << 6), A.pt.slot[q]);
+        if (!KEEP) sh.pr[w][lane] = mine;
     }
-    auto pick = [&](const float (&v)[R], int r0) GEM_INL {
-        const int r = opaque(r0);
-        float x = v[0];
-        rows<R>([&](auto uc) GEM_INL { x = decltype(uc)::value == r ? v[decltype(uc)::value] : x; });
-        return x;
+    // the rows (bits) that hold entries
+    auto rows_of = [&](int row) GEM_INL {
+        unsigned m = 0;
+        rows<R>([&](auto rc) GEM_INL { m |= __any(row == decltype(rc)::value) ? 1u << decltype(rc)::value : 0u; });
+        return m;
     };
-    auto record = [&](int r, int l, int slot, int64_t n) GEM_INL {
+    const unsigned first_rows = KEEP && pcount > 0 ? rows_of(mine.x >> 6) : 0u;
+    auto record = [&](int g, int64_t n) GEM_INL {
+        const bool on = g + lane < pcount;
+        int2 q = make_int2(0, 0);
+        if (g == 0) q = KEEP ? mine : sh.pr[w][lane];
+        else if (on) q = make_int2(A.pt.cell[pfirst + g + lane] - (w * R << 6), A.pt.slot[pfirst + g + lane]);
+        const int row = on ? q.x >> 6 : -1, col = (q.x & 63) << 2;
+        const unsigned in = KEEP ? (unsigned)opaque((int)(g == 0 ? first_rows : rows_of(row))) : 0u;
+        float v = 0.f;
+        auto take = [&](const float (&f)[R]) GEM_INL {
+            rows<R>([&](auto rc) GEM_INL {
+                constexpr int r = decltype(rc)::value;
+                if (KEEP ? (in >> r & 1) != 0 : (bool)__any(row == r)) {
+                    const float x = __int_as_float(__builtin_amdgcn_ds_bpermute(col, __float_as_int(f[r])));
+                    v = row == r ? x : v;
+                }
+            });
+        };
         // (the three conditions opaque: known to exclude one another, the
         // arrays were merged into one indexed access, in memory)
-        float v = 0.f;
-        if (opaque(p.probe_comp == FDTD_EZ)) v = pick(ez, r);
-        if (opaque(p.probe_comp == FDTD_HX)) v = pick(hx, r);
-        if (opaque(p.probe_comp == FDTD_HY)) v = pick(hy, r);
-        if (lane == l) p.rec[(int64_t)slot * p.rec_stride + (n - p.rec_base)] = v;
+        if (opaque(p.probe_comp == FDTD_EZ)) take(ez);
+        if (opaque(p.probe_comp == FDTD_HX)) take(hx);
+        if (opaque(p.probe_comp == FDTD_HY)) take(hy);
+        if (on) p.rec[(int64_t)q.y * p.rec_stride + (n - p.rec_base)] = v;
     };
 
     // design-cell capture and monitor rows
@@ -371,14 +409,7 @@ __device__ __forceinline__ void wg_tile(const Prob2D &p, const TileW &T, const W
         sval = svn;
         sh.e[(s + 1) & 1][w][0][lane] = ez[0];
         sh.e[(s + 1) & 1][w][1][lane] = ez[R - 1];
-        if (np > 0) {
-            record(pr0, pl0, ps0, step + s);
-            if (np > 1) record(pr1, pl1, ps1, step + s);
-            for (int q = prest; q < pend && np > 2; ++q) {
-                const int cell = load_const(A.pt.cell + q), pi = cell / ny, pj = cell - pi * ny;
-                if (pi >= ib && pi < ib + R) record(pi - ib, pj - T.c, load_const(A.pt.slot + q), step + s);
-            }
-        }
+        for (int g = 0; g < pcount; g += 64) record(g, step + s);
         if constexpr (XT == 2) {
             if (tapw) {
                 float *row = A.tap.ring + (int64_t)s * A.tap.npts;

@@ -1,5 +1,7 @@
 // Host-side tile plan of the 2D multi-step kernel (pure integer work).
 #include <algorithm>
+#include <array>
+#include <iterator>
 #include <vector>
 
 #include "common.hpp"
@@ -154,6 +156,58 @@ void wg2d_plan(int prob, int nx, int ny, int cls, int mat, int TB, const int *xl
     // rows together: neighbouring strips share their halo rows' lines
     std::stable_sort(t.begin(), t.end(), [](const TileW &u, const TileW &v) { return u.i0 < v.i0; });
     tiles.insert(tiles.end(), t.begin(), t.end());
+}
+
+void wg2d_probes(const std::vector<TileW> &tiles, int rows, const std::vector<WgProbe> &probes, std::vector<int> &start,
+                 std::vector<int> &cell, std::vector<int> &slot) {
+    std::vector<std::array<int, 3>> ent;  // {tile, cell, slot}
+    auto put = [&](int t, const WgProbe &p) {
+        ent.push_back({t, (p.i - tiles[(size_t)t].a) << 6 | (p.j - tiles[(size_t)t].c), p.slot});
+    };
+    if (rows > 0) {
+        for (size_t t = 0; t < tiles.size(); ++t)
+            for (const WgProbe &p : probes) {
+                const TileW &T = tiles[t];
+                if (p.prob == T.prob && p.i >= T.a && p.i < T.a + rows && p.j >= T.c && p.j < T.c + 64) put((int)t, p);
+            }
+    } else {
+        // a problem's tiles are one range; a few probes look through it,
+        // many through its tiles sorted by strip and first row
+        for (size_t u = 0, v = 0; u < probes.size(); u = v) {
+            const int prob = probes[u].prob;
+            while (v < probes.size() && probes[v].prob == prob) ++v;
+            const size_t b = (size_t)(std::lower_bound(tiles.begin(), tiles.end(), prob,
+                                                       [](const TileW &T, int q) { return T.prob < q; }) -
+                                      tiles.begin());
+            size_t e = b;
+            while (e < tiles.size() && tiles[e].prob == prob) ++e;
+            std::vector<std::array<int, 3>> at;  // {first column, first row, tile}
+            if (v - u >= 16) {
+                for (size_t t = b; t < e; ++t) at.push_back({tiles[t].j0, tiles[t].i0, (int)t});
+                std::sort(at.begin(), at.end());
+            }
+            auto last = [&](int j, int i) {  // the last tile not beyond (j, i)
+                return *std::prev(std::upper_bound(at.begin(), at.end(), std::array<int, 3>{j, i, INT32_MAX}));
+            };
+            for (size_t q = u; q < v; ++q) {
+                const WgProbe &p = probes[q];
+                size_t t = b;
+                if (!at.empty()) t = (size_t)last(last(p.j, INT32_MAX)[0], p.i)[2];
+                else while (!(p.i >= tiles[t].i0 && p.i < tiles[t].i1 && p.j >= tiles[t].j0 && p.j < tiles[t].j1)) ++t;
+                put((int)t, p);
+            }
+        }
+    }
+    std::sort(ent.begin(), ent.end());
+    start.assign(tiles.size() + 1, 0);
+    cell.clear();
+    slot.clear();
+    for (const auto &e : ent) {
+        start[(size_t)e[0] + 1]++;
+        cell.push_back(e[1]);
+        slot.push_back(e[2]);
+    }
+    for (size_t t = 0; t < tiles.size(); ++t) start[t + 1] += start[t];
 }
 
 }  // namespace gem

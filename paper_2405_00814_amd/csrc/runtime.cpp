@@ -523,20 +523,11 @@ void Sim::build_probe_tiles() {
         wg2d_plan(0, nx, ny, wg_cls, wg_mat, wg_tb, xl, yl, tl);
         wg_n = (int)tl.size();
         swap_in(wg_dev, dev_upload(al, tl.data(), tl.size(), st));
-        std::vector<std::pair<int, int>> ent;  // (owning tile, probe)
-        for (size_t q = 0; q < probe_cells.size(); ++q) {
-            const int i = (int)(probe_cells[q] / ny), j = (int)(probe_cells[q] % ny);
-            for (size_t t = 0; t < tl.size(); ++t)
-                if (i >= tl[t].i0 && i < tl[t].i1 && j >= tl[t].j0 && j < tl[t].j1) ent.push_back({(int)t, (int)q});
-        }
-        std::stable_sort(ent.begin(), ent.end());
-        std::vector<int> st2(tl.size() + 1, 0), ce, sl;
-        for (auto &e : ent) {
-            ce.push_back((int)probe_cells[(size_t)e.second]);
-            sl.push_back(e.second);
-            st2[(size_t)e.first + 1]++;
-        }
-        for (size_t t = 0; t < tl.size(); ++t) st2[t + 1] += st2[t];
+        std::vector<WgProbe> pr;
+        for (size_t q = 0; q < probe_cells.size(); ++q)
+            pr.push_back(WgProbe{0, (int)(probe_cells[q] / ny), (int)(probe_cells[q] % ny), (int)q});
+        std::vector<int> st2, ce, sl;
+        wg2d_probes(tl, 0, pr, st2, ce, sl);
         swap_in(pt2_start, dev_upload(al, st2.data(), st2.size(), st));
         swap_in(pt2_cell, dev_upload(al, ce.data(), std::max<size_t>(ce.size(), 1), st));
         swap_in(pt2_slot, dev_upload(al, sl.data(), std::max<size_t>(sl.size(), 1), st));
