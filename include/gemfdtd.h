@@ -373,8 +373,10 @@ int fdtd_last_step_time(fdtd_sim *sim, float *ms, int64_t *launches);
  * updates; psi: CPML auxiliary values it updates; cpml: 0 no CPML code, 1
  * z-slab code only, 2 x/y (and z) slab code, -1 a whole step; launches:
  * kernel launches in the entry; steps: leapfrog steps the entry advances
- * its cells by (1, or 2 for the two-step launch).  The events add a small
- * gap between launches. */
+ * its cells by (1; 2 for the two-step launch; on 2D grids those of a
+ * multi-step pass, in workgroup tiles of the first pass that fdtd_step
+ * would cut `steps` into; all of them for variant 4).  The events add a
+ * small gap between launches. */
 typedef struct {
     float ms;
     int64_t cells;

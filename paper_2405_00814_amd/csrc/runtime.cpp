@@ -1544,11 +1544,14 @@ int fdtd_step_profile(fdtd_sim *sim, int32_t steps, fdtd_launch_stat *out, int32
     if (s.is_graph) graph_ensure(s);
     const bool fused3 = s.ndim == 3 && !s.is_graph && s.kcfg.variant >= 2;
     const bool two = fused3 && s.kcfg.variant == 3 && steps >= 2;
-    const bool tb2 = s.ndim == 2 && !s.is_graph && s.kcfg.variant == 3 && steps >= s.kcfg.tile[2];
     const bool res = s.kcfg.variant == 4 && s.wg2d();
+    const bool wg = s.wg2d() && !res && steps > 1;
+    const bool tb2 = s.ndim == 2 && !s.is_graph && s.kcfg.variant == 3 && !s.wg2d() && steps >= s.kcfg.tile[2];
     // one timed unit: a step, a pair of steps for the 3D two-step pass, the
-    // TB steps of the 2D multi-step pass, or all steps (variant 4)
-    const int32_t per = two ? 2 : (tb2 ? s.kcfg.tile[2] : (res ? steps : 1));
+    // TB steps of the 2D multi-step pass, a pass of workgroup tiles as
+    // fdtd_step would cut `steps`, or all steps (variant 4)
+    const int32_t wp = wg ? (steps + s.wg_most() - 1) / s.wg_most() : 1;
+    const int32_t per = two ? 2 : (wg ? (steps + wp - 1) / wp : (tb2 ? s.kcfg.tile[2] : (res ? steps : 1)));
     const int32_t units = steps / per;
     const size_t nl = two ? s.pair_launches() : (fused3 ? s.plan3.l.size() : 1);
     // all events of all units are recorded first; one synchronisation at the end
@@ -1570,9 +1573,9 @@ int fdtd_step_profile(fdtd_sim *sim, int32_t steps, fdtd_launch_stat *out, int32
         s.last_launches = 0;
         if (two) {
             s.launch_pair(s.n_done, e);
-        } else if (tb2) {
+        } else if (wg || tb2) {
             hip_check(hipEventRecord(e[0], s.st), "event");
-            if (s.wg2d()) s.launch_wg2d(s.n_done, per);
+            if (wg) s.launch_wg2d(s.n_done, per);
             else s.launch_tb2d(s.n_done);
             hip_check(hipEventRecord(e[1], s.st), "event");
         } else if (res) {
