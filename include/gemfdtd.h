@@ -351,7 +351,8 @@ int fdtd_set_kernel(fdtd_sim *sim, const fdtd_kernel_config *cfg);
 int fdtd_get_kernel(const fdtd_sim *sim, fdtd_kernel_config *cfg);
 
 /* Time every candidate configuration on this grid for `trial_steps` steps
- * and keep the fastest (the state is saved before and restored after).
+ * (rounded up to whole passes of the candidate) and keep the one with the
+ * shortest step (the state is saved before and restored after).
  * The choice is cached in the JSON file named by $GEMFDTD_TUNE_CACHE (if
  * set) keyed by device, dimensions and material flags.  out may be NULL. */
 int fdtd_autotune(fdtd_sim *sim, int32_t trial_steps, fdtd_kernel_config *out);

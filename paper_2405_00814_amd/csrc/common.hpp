@@ -230,6 +230,10 @@ void wg2d_probes(const std::vector<TileW> &tiles, int rows, const std::vector<Wg
 // size class and steps per pass for grids (nx, ny) advanced together on
 // `cus` compute units
 void wg2d_default(const std::vector<std::pair<int, int>> &grids, int mat, int cus, int &cls, int &TB);
+// Steps of an autotuner's trial of at least `trial` steps: whole passes of
+// the candidate, which a trial of one length for all would cut alike
+// (20 steps of 10, 12 or 14 per pass: two passes of 10 each).
+int trial_steps_of(const fdtd_kernel_config &k, int ndim, int trial);
 // xt: 0 plain, 1 with a.cap, 2 with a.tap (single problem only)
 hipError_t launch_2d_wg(const WgArgs &a, int cls, int mat, int xt, hipStream_t st);
 int fused2d_ntiles(int nx, int ny, const Fused2DCfg &c);

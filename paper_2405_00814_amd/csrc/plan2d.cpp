@@ -107,6 +107,11 @@ void wg2d_default(const std::vector<std::pair<int, int>> &grids, int mat, int cu
     TB = mat == 2 ? 10 : 12;
 }
 
+int trial_steps_of(const fdtd_kernel_config &k, int ndim, int trial) {
+    const int per = k.variant != 3 ? 1 : ndim == 2 ? k.tile[2] : 2;
+    return (trial + per - 1) / per * per;
+}
+
 void wg2d_plan(int prob, int nx, int ny, int cls, int mat, int TB, const int *xlohi, const int *ylohi,
                std::vector<TileW> &tiles) {
     const WgShape sh = wg2d_shape(cls, mat);

@@ -2100,7 +2100,6 @@ int fdtd_autotune(fdtd_sim *sim, int32_t trial_steps, fdtd_kernel_config *out) {
     if (s.is_graph) fail(FDTD_EINVAL, "autotune applies to the implicit-graph stepper");
     if (s.dft.comp >= 0) fail(FDTD_ESTATE, "remove the frequency-domain monitor before autotuning");
     if (trial_steps < 2) trial_steps = 2;
-    trial_steps = (trial_steps + 3) / 4 * 4;  // whole passes of the multi-step kernels
     const std::string key = tune_key(s);
     const char *path = std::getenv("GEMFDTD_TUNE_CACHE");
     std::map<std::string, std::vector<int>> cache;
@@ -2209,11 +2208,14 @@ int fdtd_autotune(fdtd_sim *sim, int32_t trial_steps, fdtd_kernel_config *out) {
     const int64_t n_done0 = s.n_done, n_rec0 = s.n_rec;
     const int cur0 = s.cur;
     const fdtd_kernel_config k0 = s.kcfg;
-    float best = 1e30f;
+    float best = 1e30f;  // ms per step
     fdtd_kernel_config bestk = k0;
-    s.ensure_source(s.n_done + trial_steps + 4);
-    s.ensure_rec(s.n_rec + trial_steps + 4);
+    int most = 0;
+    for (const auto &k : cand) most = std::max(most, trial_steps_of(k, s.ndim, trial_steps));
+    s.ensure_source(s.n_done + most + 4);
+    s.ensure_rec(s.n_rec + most + 4);
     for (auto &k : cand) {
+        const int trial = trial_steps_of(k, s.ndim, trial_steps);
         s.kcfg = k;
         s.pt_ntiles = -1;
         s.build_probe_tiles();
@@ -2221,13 +2223,13 @@ int fdtd_autotune(fdtd_sim *sim, int32_t trial_steps, fdtd_kernel_config *out) {
         s.n_rec = n_rec0;
         s.advance(4);  // warm-up
         hip_check(hipEventRecord(s.ev0, s.st), "event");
-        s.advance(trial_steps);
+        s.advance(trial);
         hip_check(hipEventRecord(s.ev1, s.st), "event");
         hip_check(hipEventSynchronize(s.ev1), "sync");
         float ms = 0;
         hip_check(hipEventElapsedTime(&ms, s.ev0, s.ev1), "elapsed");
-        if (ms < best) {
-            best = ms;
+        if (ms / trial < best) {
+            best = ms / trial;
             bestk = k;
         }
         s.cur = cur0;
