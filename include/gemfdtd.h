@@ -354,7 +354,9 @@ int fdtd_get_kernel(const fdtd_sim *sim, fdtd_kernel_config *cfg);
  * (rounded up to whole passes of the candidate) and keep the one with the
  * shortest step (the state is saved before and restored after).
  * The choice is cached in the JSON file named by $GEMFDTD_TUNE_CACHE (if
- * set) keyed by device, dimensions and material flags.  out may be NULL. */
+ * set) keyed by device, dimensions, material flags and the library's set of
+ * candidates (a choice among other candidates is kept in the file and not
+ * used).  out may be NULL. */
 int fdtd_autotune(fdtd_sim *sim, int32_t trial_steps, fdtd_kernel_config *out);
 
 /* Device time in milliseconds of the kernels enqueued by the last
@@ -423,8 +425,9 @@ int fdtd_batch_set_kernel(fdtd_batch *b, int32_t tb, int32_t tx, int32_t vmax, i
  * problems' state, step count and probe record lengths are saved before and
  * restored after (the batch continues as if the call had not been made).
  * The choice is cached in the JSON file named by $GEMFDTD_TUNE_CACHE (if
- * set) under the device and the batch's size mix (count, cells, the sorted
- * list of dimensions and material kinds) and reused without timing.
+ * set) under the device, the batch's size mix (count, cells, the sorted
+ * list of dimensions and material kinds) and the library's set of
+ * candidates, and reused without timing.
  * out (4 int32, may be NULL): the chosen tb, tx, vmax, txo.  Synchronises.
  * Device memory: a copy of the state while it runs. */
 int fdtd_batch_autotune(fdtd_batch *b, int32_t trial_steps, int32_t *out);

@@ -557,8 +557,8 @@ int fdtd_batch_autotune(fdtd_batch *b, int32_t trial_steps, int32_t *out) {
                 h *= 1099511628211ull;
             }
         char key[160];
-        snprintf(key, sizeof key, "%s|batch|n%zu|c%lld|h%016llx", arch.c_str(), dims.size(), (long long)cells,
-                 (unsigned long long)h);
+        snprintf(key, sizeof key, "%s|batch|n%zu|c%lld|h%016llx|K%d", arch.c_str(), dims.size(), (long long)cells,
+                 (unsigned long long)h, kTuneSet);
         const char *path = std::getenv("GEMFDTD_TUNE_CACHE");
         std::map<std::string, std::vector<int>> cache;
         if (path) cache = read_cache(path);

@@ -1208,7 +1208,8 @@ static std::string tune_key(const Sim &s) {
     if (hipGetDeviceProperties(&pr, s.device) == hipSuccess) arch = pr.gcnArchName;
     std::ostringstream o;
     o << arch << "|" << s.ndim << "|" << s.nx << "x" << s.ny << "x" << s.nz << "|L" << s.lossy << "|M"
-      << s.mumap << "|P" << (s.ax[0].lo + s.ax[0].hi + s.ax[1].lo + s.ax[1].hi + s.ax[2].lo + s.ax[2].hi > 0);
+      << s.mumap << "|P" << (s.ax[0].lo + s.ax[0].hi + s.ax[1].lo + s.ax[1].hi + s.ax[2].lo + s.ax[2].hi > 0)
+      << "|K" << kTuneSet;
     return o.str();
 }
 

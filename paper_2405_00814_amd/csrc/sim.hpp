@@ -45,6 +45,12 @@ struct DevAlloc {
 // 200^3 193 (184), 201x199x197 198 (235).
 constexpr int64_t kFlatMaxCells4 = (int64_t)1 << 22, kFlatMaxCells = (int64_t)1 << 23;
 
+// The autotuners' set of candidates, part of their cache keys: a choice made
+// among others (the marching kernels, before there were workgroup tiles and
+// one thread per cell) is not taken for one among these.  Raised with every
+// change of the candidates or of what a configuration runs.
+constexpr int kTuneSet = 2;
+
 // One axis of CPML tables in double precision before rounding.
 struct AxisHost {
     int n = 0, lo = 0, hi = 0;
