@@ -53,6 +53,7 @@ static void copy_state(Sim &s, int set, float *buf, bool to_buf) {
     for (int f : {FDTD_EZ, FDTD_HX, FDTD_HY}) mv(s.f[set][f], s.ncell);
     for (int a = 0; a < 4; ++a) mv(s.psi[set][a], s.psi_len[a]);
     hip_check(launch_copy_parts(c, s.st), "state copy");
+    s.last_launches += 1;
 }
 
 static int64_t state_floats(const Sim &s) {
@@ -219,6 +220,7 @@ static int adjoint_run(fdtd_sim *sim, int64_t T, int64_t n0, int64_t n1, const i
                                               cap->br + (k - k0) * ndc, s.split2d() ? &sp : nullptr),
                               "forward step");
                     s.cur = 1 - s.cur;
+                    s.last_launches += s.split2d() ? (s.tl2_inner > 0) + (s.tl2_outer > 0) : 1;
                 } else {
                     s.launch_step(k);
                 }
@@ -227,6 +229,7 @@ static int adjoint_run(fdtd_sim *sim, int64_t T, int64_t n0, int64_t n1, const i
                 k += 1;
             }
         };
+        s.last_launches = 0;
         hip_check(hipEventRecord(s.ev0, s.st), "event");
         // ---- forward: checkpoints, then the last segment with its design values ----
         for (int64_t g = 0; g < nseg; ++g) {
@@ -419,13 +422,14 @@ static int adjoint_run(fdtd_sim *sim, int64_t T, int64_t n0, int64_t n1, const i
             if (g >= 1) recompute(g - 1);
             if (g + 1 < nseg) hip_check(hipStreamWaitEvent(st0, ev_rec[b], 0), "stream wait");
             const Prob2D p = s.prob2d(0, 0);
+            // the first step's input is seeded here, every later one by the
+            // launch that writes it
+            if (k1 == T && T > n0 && T <= n1) {
+                hip_check(launch_adj2d_seed(a[acur].ez, d_ust, d_pcell, d_pslot, nu, rec_snap, s.rec_cap, T - 1, st0),
+                          "adjoint seed");
+                s.last_launches += 1;
+            }
             for (int64_t k = k1 - 1; awg && k >= k0;) {
-                // the first step's input is seeded here, every later one by
-                // the pass that writes it
-                if (k == T - 1 && T > n0 && T <= n1)
-                    hip_check(launch_adj2d_seed(a[acur].ez, d_ust, d_pcell, d_pslot, nu, rec_snap, s.rec_cap, T - 1,
-                                                st0),
-                              "adjoint seed");
                 const int64_t left = k - k0 + 1, most = wtl.size() == 1 ? left : atb, np = (left + most - 1) / most;
                 AdjWArgs w{};
                 w.p = p;
@@ -451,21 +455,17 @@ static int adjoint_run(fdtd_sim *sim, int64_t T, int64_t n0, int64_t n1, const i
                 w.rec = rec_snap;
                 w.rec_stride = s.rec_cap;
                 hip_check(launch_adj2d_wg(w, acls, s.mat(), st0), "adjoint steps");
+                s.last_launches += 1;
                 acur = 1 - acur;
                 k -= w.nsteps;
             }
             for (int64_t k = k1 - 1; !awg && k >= k0; --k) {
-                // the first step's input is seeded here, every later one by
-                // the step that writes it
-                if (k == T - 1 && T > n0 && T <= n1)
-                    hip_check(launch_adj2d_seed(a[acur].ez, d_ust, d_pcell, d_pslot, nu, rec_snap, s.rec_cap, T - 1,
-                                                st0),
-                              "adjoint seed");
                 const int seed_out = (k > n0 && k <= n1) ? 1 : 0;
                 hip_check(launch_adj2d_fused(p, a[acur], a[1 - acur], dbox, cbox, cap_ez[b] + (k - k0) * ndc,
                                              cap_br[b] + (k - k0) * ndc, sez, sbr, shx, shy, seed_out, apt,
                                              rec_snap, s.rec_cap, k - 1, ac.V, ac.TX, st0),
                           "adjoint step");
+                s.last_launches += 1;
                 acur = 1 - acur;
             }
             if (rs) hip_check(hipEventRecord(ev_adj[b], st0), "event");
@@ -487,7 +487,7 @@ static int adjoint_run(fdtd_sim *sim, int64_t T, int64_t n0, int64_t n1, const i
         s.n_rec = T;
         hip_check(hipEventRecord(s.ev1, s.st), "event");
         s.timed = true;
-        s.last_launches = T * 3 + 1;
+        for (const float *g : {grad_eps_dev, grad_sigma_dev, grad_mu_dev}) s.last_launches += g != nullptr;
         hip_check(hipStreamSynchronize(s.st), "sync");
         release_streams();
         for (void *p : tmp) s.al.put(p);
