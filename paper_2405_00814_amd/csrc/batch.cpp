@@ -81,7 +81,7 @@ struct fdtd_batch {
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     bool timed = false;
     int64_t last_launches = 0;
-    bool probes_dirty = true;
+    bool probes_dirty = true, tiles_ok = false;
 
     ~fdtd_batch() {
         if (exec) (void)hipGraphExecDestroy(exec);
@@ -103,6 +103,15 @@ struct BFail {
 };
 
 static void batch_build_probes(fdtd_batch &b) {
+    b.probes_dirty = true;  // until the end: a failure leaves them to the next step call
+    // a pointer kept beyond its block would give back, next time, whatever
+    // block has that address by then
+    auto release = [&](auto &g) {
+        for (int **p : {&g.pt_start, &g.pt_cell, &g.pt_slot}) {
+            b.al.put(*p);
+            *p = nullptr;
+        }
+    };
     if (b.wg.TB > 0) {
         std::vector<WgProbe> pr;
         for (size_t q = 0; q < b.sims.size(); ++q) {
@@ -113,10 +122,7 @@ static void batch_build_probes(fdtd_batch &b) {
         std::vector<int> start, cell, slot;
         wg2d_probes(b.wg.list, 0, pr, start, cell, slot);
         if (cell.empty()) cell.push_back(0), slot.push_back(0);
-        b.al.put(b.wg.pt_start);
-        b.al.put(b.wg.pt_cell);
-        b.al.put(b.wg.pt_slot);
-        b.wg.pt_start = b.wg.pt_cell = b.wg.pt_slot = nullptr;
+        release(b.wg);
         b.wg.pt_start = (int *)b.al.get(start.size() * 4);
         b.wg.pt_cell = (int *)b.al.get(cell.size() * 4);
         b.wg.pt_slot = (int *)b.al.get(slot.size() * 4);
@@ -152,9 +158,7 @@ static void batch_build_probes(fdtd_batch &b) {
             cell.push_back(0);
             slot.push_back(0);
         }
-        b.al.put(g.pt_start);
-        b.al.put(g.pt_cell);
-        b.al.put(g.pt_slot);
+        release(g);
         g.pt_start = (int *)b.al.get(start.size() * 4);
         g.pt_cell = (int *)b.al.get(cell.size() * 4);
         g.pt_slot = (int *)b.al.get(slot.size() * 4);
@@ -192,9 +196,7 @@ static void batch_build_probes(fdtd_batch &b) {
             cell.push_back(0);
             slot.push_back(0);
         }
-        b.al.put(g.pt_start);
-        b.al.put(g.pt_cell);
-        b.al.put(g.pt_slot);
+        release(g);
         g.pt_start = (int *)b.al.get(start.size() * 4);
         g.pt_cell = (int *)b.al.get(cell.size() * 4);
         g.pt_slot = (int *)b.al.get(slot.size() * 4);
@@ -243,6 +245,8 @@ static void batch_sync_probs(fdtd_batch &b) {
 // multi-step groups: vector width 4, 2 or 1 by row length (at most
 // tb_vmax); none when tb == 1
 static void batch_build_tb(fdtd_batch &b) {
+    b.tiles_ok = false;  // until the end, likewise
+    b.probes_dirty = true;
     for (auto &g : b.tbg) {
         b.al.put(g.tiles);
         b.al.put(g.pt_start);
@@ -255,7 +259,10 @@ static void batch_build_tb(fdtd_batch &b) {
     b.al.put(b.wg.pt_cell);
     b.al.put(b.wg.pt_slot);
     b.wg = WgGroup{};
-    if (b.tb <= 1) return;
+    if (b.tb <= 1) {
+        b.tiles_ok = true;
+        return;
+    }
     const int n = (int)b.sims.size();
     // the default configuration: workgroup tiles, where every problem's rows
     // and slabs fit their offsets
@@ -285,6 +292,7 @@ static void batch_build_tb(fdtd_batch &b) {
                       "upload");
             hip_check(hipStreamSynchronize(b.st), "sync");
             b.wg = w;
+            b.tiles_ok = true;
             return;
         }
     }
@@ -334,6 +342,7 @@ static void batch_build_tb(fdtd_batch &b) {
         hip_check(hipStreamSynchronize(b.st), "sync");
         b.tbg.push_back(g);
     }
+    b.tiles_ok = true;
 }
 
 static void batch_launch_one(fdtd_batch &b, int parity, int k, hipStream_t st) {
@@ -672,9 +681,8 @@ int fdtd_batch_set_source(fdtd_batch *b, int32_t problem, const int32_t *ijk, in
 int fdtd_batch_set_probes(fdtd_batch *b, int32_t problem, const int32_t *ijk, int32_t n) {
     try {
         fdtd_sim *h = batch_sim(b, problem);
-        const int rc = fdtd_set_probes(h, FDTD_EZ, ijk, n);
-        if (rc == FDTD_OK) b->probes_dirty = true;
-        return rc;
+        b->probes_dirty = true;  // (a call that fails may have replaced them all the same)
+        return fdtd_set_probes(h, FDTD_EZ, ijk, n);
     } catch (...) {
         return gem::status_of_current_exception();
     }
@@ -688,6 +696,7 @@ int fdtd_batch_step(fdtd_batch *b, int64_t n) {
             sp->ensure_source(b->n_done + n);
             sp->ensure_rec(sp->n_rec + n);
         }
+        if (!b->tiles_ok) batch_build_tb(*b);
         if (b->probes_dirty) batch_build_probes(*b);
         batch_sync_probs(*b);
         hip_check(hipMemcpyAsync(b->step_base, &b->n_done, sizeof(int64_t), hipMemcpyHostToDevice, b->st), "upload");

@@ -153,3 +153,36 @@ def test_set_probes(budget, form):
         assert np.array_equal(u, v)
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("cfg", [(4, 16, 1, 0), (2, 8, 2, 0), (1, 16, 1, 0)])
+def test_batch_set_kernel_and_probes(budget, cfg):
+    """A batch whose tile or probe lists did not fit builds them before it
+    steps: no step is left out, no record written past its end."""
+    from paper_2405_00814_amd.sim import Batch
+    probs = W.batch2d(count=3, steps=0, seed=5, side=(70, 120), nprobes=5, rect_side=(8, 40), rect_density=40.0 / 4096)
+    a, b = Batch(probs), Batch(probs)
+    for x in (a, b):
+        x.step(10)
+    cells = probs[1].probes[:2]
+    calls = [(lambda x: x.set_kernel(*cfg), 1e-5), (lambda x: x.set_probes(1, cells), 1e-5)]
+    for call, tol in calls:
+        failed = 0
+        for k in _fails_until_it_fits(budget, lambda: call(a)):
+            failed += 1
+            a.step(13)
+            b.step(13)
+            for q in range(3):
+                for f in ("ez", "hx", "hy"):
+                    u, v = a.get_field(q, f), b.get_field(q, f)
+                    assert np.linalg.norm(u - v) <= tol * np.linalg.norm(v), (k, q, f)
+        assert failed
+        call(b)
+    for x in (a, b):
+        x.step(9)
+    for q in range(3):
+        u, v = a.probe(q), b.probe(q)
+        assert u.shape[0] == v.shape[0] == (2 if q == 1 else 5)
+        assert np.allclose(u[:, -9:], v[:, -9:], rtol=1e-4, atol=1e-6 * np.abs(v).max()), q
+    a.close()
+    b.close()
