@@ -1698,21 +1698,28 @@ int fdtd_set_dft(fdtd_sim *sim, int component, const int32_t *lo, const int32_t 
     const int b[6] = {lo[0], hi[0], lo[1], hi[1], s.ndim == 3 ? lo[2] : 0, s.ndim == 3 ? hi[2] : 1};
     for (int q = 0; q < 6; ++q) d.box[q] = b[q];
     d.npts = (int64_t)(b[1] - b[0]) * (b[3] - b[2]) * (b[5] - b[4]);
-    if (s.is_graph) {  // the graph's node order is not the box's: an index list
-        std::vector<int64_t> idx;
-        for (int i = b[0]; i < b[1]; ++i)
-            for (int j = b[2]; j < b[3]; ++j) idx.push_back(graph_node(s, component, i, j));
-        d.idx = dev_upload(s.al, idx.data(), idx.size(), s.st);
-    }
-    d.acc = (double *)s.al.get((size_t)(2 * nf * d.npts) * 8);  // zero-filled
-    if (s.ndim == 2 && !s.is_graph) {  // (a full pass of the workgroup tiles, if there is the memory)
-        try {
-            d.ring = (float *)s.al.get((size_t)(kDftBatch * d.npts) * 4);
-            d.rows = kDftBatch;
-        } catch (const Fail &) {
+    try {
+        if (s.is_graph) {  // the graph's node order is not the box's: an index list
+            std::vector<int64_t> idx;
+            for (int i = b[0]; i < b[1]; ++i)
+                for (int j = b[2]; j < b[3]; ++j) idx.push_back(graph_node(s, component, i, j));
+            d.idx = dev_upload(s.al, idx.data(), idx.size(), s.st);
         }
+        d.acc = (double *)s.al.get((size_t)(2 * nf * d.npts) * 8);  // zero-filled
+        if (s.ndim == 2 && !s.is_graph) {  // (a full pass of the workgroup tiles, if there is the memory)
+            try {
+                d.ring = (float *)s.al.get((size_t)(kDftBatch * d.npts) * 4);
+                d.rows = kDftBatch;
+            } catch (const Fail &) {
+            }
+        }
+        if (!d.ring) d.ring = (float *)s.al.get((size_t)(d.rows * d.npts) * 4);
+    } catch (...) {  // no monitor, rather than one without its arrays
+        s.al.put(d.idx);
+        s.al.put(d.acc);
+        s.dft = Sim::Dft{};
+        throw;
     }
-    if (!d.ring) d.ring = (float *)s.al.get((size_t)(d.rows * d.npts) * 4);
     hip_check(hipStreamSynchronize(s.st), "sync");
     return FDTD_OK;
     GEM_CATCH

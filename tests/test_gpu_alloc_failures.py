@@ -186,3 +186,34 @@ def test_batch_set_kernel_and_probes(budget, cfg):
         assert np.allclose(u[:, -9:], v[:, -9:], rtol=1e-4, atol=1e-6 * np.abs(v).max()), q
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("form", ["tiles", "single", "graph"])
+def test_set_dft(budget, form):
+    """A monitor whose arrays did not fit is no monitor."""
+    from paper_2405_00814_amd import _lib as L
+    from paper_2405_00814_amd.sim import Sim
+    pb = _problem(2)
+    a, b = (Sim.from_problem(pb, graph=form == "graph") for _ in range(2))
+    if form == "single":
+        for s in (a, b):
+            s.set_kernel(2)
+    for s in (a, b):
+        s.step(20)
+    mon = ("ez", (10, 12), (60, 50), [1e9, 2e9])
+    failed = 0
+    for k in _fails_until_it_fits(budget, lambda: a.set_dft(*mon)):
+        failed += 1
+        for s in (a, b):
+            s.step(5)
+        for u, v in zip(_state(a, ("ez", "hx", "hy")), _state(b, ("ez", "hx", "hy"))):
+            assert np.array_equal(u, v), k
+        with pytest.raises(L.FdtdError):
+            a.get_dft()
+    assert failed
+    b.set_dft(*mon)
+    for s in (a, b):
+        s.step(31)
+    assert np.array_equal(a.get_dft()[0], b.get_dft()[0])
+    a.close()
+    b.close()
