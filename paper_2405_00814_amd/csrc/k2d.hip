@@ -132,8 +132,9 @@ hipError_t launch_2d_ref(const Prob2D &p, int64_t step, hipStream_t st) {
 // s1, so neighbouring strips never see half-updated values.
 // ---------------------------------------------------------------------------
 // One wavefront tile: x rows [cx*TX, cx*TX + TX) of the strip sy.  Probe
-// entries [pbeg, pend) of pt belong to this tile.
-template <int V, bool PML, bool CAPTURE>
+// entries [pbeg, pend) of pt belong to this tile.  MAP: 0 = no Db map, 1 =
+// with one, 2 = as the problem says (batch).
+template <int V, bool PML, bool CAPTURE, int MAP>
 __device__ __forceinline__ void fused2d_tile(const Prob2D &p, int TX, int cx, int sy,
                                              const ProbeTiles &pt, int pbeg, int pend,
                                              int64_t step, int4 design, float *cap_ez,
@@ -150,7 +151,12 @@ __device__ __forceinline__ void fused2d_tile(const Prob2D &p, int TX, int cx, in
     const bool valid = jb < ny;    // ny % V == 0: all V columns valid or none
     const int syw = p.y.lo + p.y.hi;
     const bool lossy = p.ca != nullptr;
-    const bool mumap = p.db != nullptr;
+    // the Db map's arithmetic by instance: chosen per cell inside the row
+    // loop, the branch cut the loads off from what could overlap them
+    // (1500^2 with CPML 23.7 us per step, 22.0 so); its loads behind a test
+    // in either case (2400x2500 with a map 46.8 us, 49.0 without the test)
+    const bool dbm = MAP != 0 && p.db != nullptr;
+    const bool mumap = MAP == 2 ? dbm : MAP == 1;
     // the source box, read once (the batched tiles read p from memory): an
     // empty box without a source
     const bool hs = p.src_idx >= 0;
@@ -196,7 +202,7 @@ __device__ __forceinline__ void fused2d_tile(const Prob2D &p, int TX, int cx, in
         float ez_m[V], hy_o[V], db[V];
         ldv<V>(ez_m, p.s0.ez + row + jb);
         ldv<V>(hy_o, p.s0.hy + row + jb);
-        if (mumap) ldv<V>(db, p.db + row + jb);
+        if (dbm) ldv<V>(db, p.db + row + jb);
         else {
 #pragma unroll
             for (int v = 0; v < V; ++v) db[v] = p.db0;
@@ -229,7 +235,7 @@ __device__ __forceinline__ void fused2d_tile(const Prob2D &p, int TX, int cx, in
             ldv<V>(s_hy, p.s0.hy + rp + jb);
             ldv<V>(s_cb, p.cb + rp + jb);
             if (lossy) ldv<V>(s_ca, p.ca + rp + jb);
-            if (mumap) ldv<V>(s_db, p.db + rp + jb);
+            if (dbm) ldv<V>(s_db, p.db + rp + jb);
         }
     };
     load_row(x0);
@@ -285,11 +291,11 @@ __device__ __forceinline__ void fused2d_tile(const Prob2D &p, int TX, int cx, in
             if (jm >= 0) {
                 const float ez_mm = p.s0.ez[row + jm];
                 const float hxo = p.s0.hx[row + jm];
-                const float dbm = mumap ? p.db[row + jm] : p.db0;
+                const float dbl = dbm ? p.db[row + jm] : p.db0;
                 const float dEy = ez_c[0] - ez_mm;
                 const bool in = PML && jj_m >= 0;
                 const float ps = in ? __builtin_fmaf(cHy_m, dEy, bHy_m * p.s0.psi_hx[(int64_t)i * syw + jj_m]) : 0.f;
-                shl = h_next(hxo, -1.f, dbm, p.db0 * kHy_m, kHy_m, dEy, mumap, in, ps);
+                shl = h_next(hxo, -1.f, dbl, p.db0 * kHy_m, kHy_m, dEy, mumap, in, ps);
             }
         }
         hx_l[0] = shl;
@@ -352,7 +358,7 @@ __device__ __forceinline__ void fused2d_tile(const Prob2D &p, int TX, int cx, in
     }
 }
 
-template <int V, bool PML, bool CAPTURE>
+template <int V, bool PML, bool CAPTURE, int MAP>
 // list: tile ids of this launch (nullptr: tiles 0 .. ntiles-1)
 __global__ __launch_bounds__(256) void k2d_fused(Prob2D p, int TX, int nsy, int ntiles,
                                                  const int *list, ProbeTiles pt, int64_t step,
@@ -363,7 +369,7 @@ __global__ __launch_bounds__(256) void k2d_fused(Prob2D p, int TX, int nsy, int 
     if (tw >= ntiles) return;  // whole wavefront leaves; no block barriers below
     const int t = list ? list[tw] : tw;
     const int cx = t / nsy, sy = t - cx * nsy;
-    fused2d_tile<V, PML, CAPTURE>(p, TX, cx, sy, pt, pt.start[t], pt.start[t + 1], step, design,
+    fused2d_tile<V, PML, CAPTURE, MAP>(p, TX, cx, sy, pt, pt.start[t], pt.start[t + 1], step, design,
                                   cap_ez, cap_br);
 }
 
@@ -383,7 +389,7 @@ __global__ __launch_bounds__(256) void k2d_batch(const Prob2D *__restrict__ prob
     const int t = t0 + tw;
     const BatchTile bt = tiles[t];
     const int64_t step = *step_base + k;
-    fused2d_tile<V, PML, false>(probs[bt.prob], TX, bt.cx, bt.sy, pt, pt.start[t],
+    fused2d_tile<V, PML, false, 2>(probs[bt.prob], TX, bt.cx, bt.sy, pt, pt.start[t],
                                  pt.start[t + 1], step, make_int4(0, 0, 0, 0), nullptr, nullptr);
 }
 
@@ -442,8 +448,12 @@ static void go2d(const Prob2D &p, const Fused2DCfg &c, const int *list, int ntil
     if (ntiles <= 0) return;
     const int nsy = (p.ny + 64 * V - 1) / (64 * V);
     const unsigned nb = (unsigned)((ntiles + 3) / 4);
-    hipLaunchKernelGGL((k2d_fused<V, PML, CAP>), dim3(nb), dim3(256), 0, st, p, c.TX, nsy, ntiles, list,
-                       pt, step, d, ce, cbr);
+    if (p.db)
+        hipLaunchKernelGGL((k2d_fused<V, PML, CAP, 1>), dim3(nb), dim3(256), 0, st, p, c.TX, nsy, ntiles, list, pt,
+                           step, d, ce, cbr);
+    else
+        hipLaunchKernelGGL((k2d_fused<V, PML, CAP, 0>), dim3(nb), dim3(256), 0, st, p, c.TX, nsy, ntiles, list, pt,
+                           step, d, ce, cbr);
 }
 
 hipError_t launch_2d_fused(const Prob2D &p, const Fused2DCfg &c, const ProbeTiles &pt,
