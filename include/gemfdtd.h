@@ -337,7 +337,8 @@ int fdtd_set_material(fdtd_sim *sim, const int32_t *lo, const int32_t *hi,
  *    steps of the pass and recomputes a halo of TB cells; one launch per
  *    pass; the n steps of a call are split into passes of nearly equal
  *    length, and a grid that fits one tile takes them all in one.  A call
- *    of one step runs the single-step kernel, with the same bits.  The
+ *    of one step (of a few on long grids of few rows) runs the single-step
+ *    kernel, with the same bits.  The
  *    default for 2D grids (not for grids of less than 40 rows and 1.5 M
  *    cells or more, and ny up to 2^20).
  * FDTD_EINVAL for unknown or unsupported combinations. */

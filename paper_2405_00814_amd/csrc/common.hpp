@@ -230,6 +230,9 @@ void wg2d_probes(const std::vector<TileW> &tiles, int rows, const std::vector<Wg
 // size class and steps per pass for grids (nx, ny) advanced together on
 // `cus` compute units
 void wg2d_default(const std::vector<std::pair<int, int>> &grids, int mat, int cus, int &cls, int &TB);
+// Fewest steps of a pass with which tiles (size class 0, ntiles of them)
+// are faster than single steps; 16: none.
+int wg2d_least(int nx, int ntiles, int cus);
 // Steps of an autotuner's trial of at least `trial` steps: whole passes of
 // the candidate, which a trial of one length for all would cut alike
 // (20 steps of 10, 12 or 14 per pass: two passes of 10 each).

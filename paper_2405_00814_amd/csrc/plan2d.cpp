@@ -93,7 +93,10 @@ void wg2d_default(const std::vector<std::pair<int, int>> &grids, int mat, int cu
         for (const auto &g : grids) n += (int64_t)along(g.first, h, tb) * along(g.second, 64, tb);
         return n;
     };
-    if (count(32, 12) <= 2 * (int64_t)cus) {
+    // (a grid of at most 32 rows would leave the rest of taller tiles empty:
+    // 8x100000 2.9 us per step in passes of 12, 4.4 in tiles of 56 rows)
+    const bool thin = std::all_of(grids.begin(), grids.end(), [](const auto &g) { return g.first <= 32; });
+    if (thin || count(32, 12) <= 2 * (int64_t)cus) {
         cls = 0;
         TB = count(32, 14) <= cus ? 14 : 12;
         return;
@@ -105,6 +108,20 @@ void wg2d_default(const std::vector<std::pair<int, int>> &grids, int mat, int cu
     }
     cls = 2;
     TB = mat == 2 ? 10 : 12;
+}
+
+// A pass moves and computes all 32 rows of its tiles, a single step the
+// grid's own.  On grids of few rows with more than two tiles per CU, us
+// with r = tiles per CU: a pass of k steps 3 + r (1.5 + 0.16 k), a single
+// step 3.1 + 0.058 r nx (3x80000, r = 7.8: calls of 3 steps 1.15 times a
+// single step's time in tiles, of 4 0.97; 8x80000: of 2 1.23, of 3 0.96;
+// 12x80000: of 2 1.07; 16x80000: of 2 0.87).
+int wg2d_least(int nx, int ntiles, int cus) {
+    const double r = (double)ntiles / cus;
+    if (nx > 32 || r <= 2) return 2;
+    for (int k = 2; k <= 15; ++k)
+        if (3 + r * (1.5 + 0.16 * k) <= k * (3.1 + 0.058 * r * nx)) return k;
+    return 16;
 }
 
 int trial_steps_of(const fdtd_kernel_config &k, int ndim, int trial) {

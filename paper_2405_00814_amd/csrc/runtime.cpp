@@ -853,7 +853,7 @@ void Sim::advance(int64_t n) {
     // a frequency-domain monitor needs every step's field: single steps
     const bool mon = dft.comp >= 0;
     const bool two = kcfg.variant == 3 && ndim == 3 && !is_graph && !mon;
-    const bool wg = wg2d() && n > 1;
+    const bool wg = wg_pass(n) > 0;
     const bool tb2 = kcfg.variant == 3 && ndim == 2 && !is_graph && !mon && !wg2d();
     const int64_t inc = probe_cells.empty() ? 0 : 1;
     int64_t q = 0;
@@ -1545,14 +1545,13 @@ int fdtd_step_profile(fdtd_sim *sim, int32_t steps, fdtd_launch_stat *out, int32
     if (s.is_graph) graph_ensure(s);
     const bool fused3 = s.ndim == 3 && !s.is_graph && s.kcfg.variant >= 2;
     const bool two = fused3 && s.kcfg.variant == 3 && steps >= 2;
-    const bool res = s.kcfg.variant == 4 && s.wg2d();
-    const bool wg = s.wg2d() && !res && steps > 1;
+    const bool res = s.kcfg.variant == 4 && s.wg_pass(steps) > 0;
+    const bool wg = s.wg_pass(steps) > 0 && !res;
     const bool tb2 = s.ndim == 2 && !s.is_graph && s.kcfg.variant == 3 && !s.wg2d() && steps >= s.kcfg.tile[2];
     // one timed unit: a step, a pair of steps for the 3D two-step pass, the
     // TB steps of the 2D multi-step pass, a pass of workgroup tiles as
     // fdtd_step would cut `steps`, or all steps (variant 4)
-    const int32_t wp = wg ? (steps + s.wg_most() - 1) / s.wg_most() : 1;
-    const int32_t per = two ? 2 : (wg ? (steps + wp - 1) / wp : (tb2 ? s.kcfg.tile[2] : (res ? steps : 1)));
+    const int32_t per = two ? 2 : (wg ? s.wg_pass(steps) : (tb2 ? s.kcfg.tile[2] : (res ? steps : 1)));
     const int32_t units = steps / per;
     const size_t nl = two ? s.pair_launches() : (fused3 ? s.plan3.l.size() : 1);
     // all events of all units are recorded first; one synchronisation at the end

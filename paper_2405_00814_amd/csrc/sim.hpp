@@ -151,6 +151,13 @@ struct Sim {
     }
     // most steps per pass: a grid in one tile has no halo to use up
     int wg_most() const { return wg_n == 1 ? 65536 : wg_tb; }
+    // steps of the first pass of a call of n steps; 0: single steps
+    int wg_pass(int64_t n) const {
+        if (!wg2d() || n < 2) return 0;
+        const int64_t np = (n + wg_most() - 1) / wg_most();
+        const int k = (int)((n + np - 1) / np);
+        return wg_cls == 0 && k < wg2d_least(nx, wg_n, cus) ? 0 : k;
+    }
     int mat() const { return mumap ? 2 : (lossy ? 1 : 0); }
     // the maps as the workgroup tiles count them (3: Db without Ca)
     int wmat() const { return mumap && !lossy ? 3 : mat(); }

@@ -1,4 +1,5 @@
-"""Host logic: the autotuner's trial lengths.  Builds
+"""Host logic: the autotuner's trial lengths and the fewest steps of a pass.
+Builds
 tests/plan_check_tune.cpp with the library's plan source (host code only) and
 runs it."""
 import os
@@ -10,7 +11,7 @@ from test_plan3d import CSRC, HERE, HIPCC, ROOT
 
 
 @pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not installed")
-def test_trials_are_whole_passes(tmp_path):
+def test_trials_and_passes(tmp_path):
     exe = str(tmp_path / "plan_check_tune")
     cmd = [HIPCC, "-O1", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I", CSRC, "-I",
            os.path.join(ROOT, "include"), os.path.join(HERE, "plan_check_tune.cpp"),
