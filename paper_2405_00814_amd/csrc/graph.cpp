@@ -35,6 +35,12 @@ struct RowBuilder {
         col.push_back((int)c);
         w.push_back((float)v);
     }
+    void reserve(int64_t rows, int64_t edges) {
+        rowptr.reserve((size_t)rows + 1);
+        dst.reserve((size_t)rows);
+        col.reserve((size_t)edges);
+        w.reserve((size_t)edges);
+    }
     void end_row(int64_t d) {
         dst.push_back((int)d);
         rowptr.push_back((int)col.size());
@@ -189,6 +195,7 @@ static void put_layer(Sim &s, Sim::Graph::Layer &L, RowBuilder &m, RowBuilder *a
                 fail(FDTD_EINVAL, "graph builder: an auxiliary row must start with its own node");
         }
         RowBuilder g;
+        g.reserve((int64_t)m.dst.size(), (int64_t)(m.col.size() + aux->col.size()));
         for (size_t r = 0; r < m.dst.size(); ++r) {
             for (int q = m.rowptr[r]; q < m.rowptr[r + 1]; ++q) {
                 const int c = m.col[(size_t)q];
@@ -269,6 +276,8 @@ static void build_graph_split(Sim &s) {
     auto ca_of = [&](int64_t c) { return (1.0 - sh(c)) / (1.0 + sh(c)); };
     auto db_of = [&](int64_t c) { return s.dt / (kMu0 * (s.mu_r.empty() ? 1.0 : s.mu_r[(size_t)c])); };
     RowBuilder hm, em;
+    hm.reserve(nnodes / 2, 5 * (nnodes / 2));
+    em.reserve(nnodes / 2, 3 * (nnodes / 2));
     for (int j = 0; j < ny; ++j) {
         for (int i = 0; i < nx; ++i) {  // Hx: -Db c_H,y (Ez(i, j+1) - Ez(i, j)) / dy
             const double w = db_of(cell(i, j)) * (double)Y.cH[j] * (double)Y.kH[j];
@@ -400,6 +409,11 @@ void build_graph(Sim &s) {
     auto pezx = [&](int ii, int j) { return o_ezx + (int64_t)j * sx + ii; };
     auto pezy = [&](int i, int jj) { return o_ezy + (int64_t)jj * nx + i; };
     RowBuilder ha, hm, ea, em;
+    const int64_t slab = (int64_t)nx * sy + (int64_t)ny * sx;
+    ha.reserve(slab, 3 * slab);
+    hm.reserve(2 * N, 6 * N + slab);
+    ea.reserve(slab, 3 * slab);
+    em.reserve(N, 5 * N + slab);
     // Field rows in increasing destination order within each layer; the
     // auxiliary rows in the order of the field rows that read them.
     // H layer, auxiliary rows
