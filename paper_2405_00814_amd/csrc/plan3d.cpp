@@ -74,6 +74,9 @@ void wave3d_plan(int nx, int ny, int nz, const Fused3DCfg &c, const int *xlohi, 
         l.pxy = pxy;
         l.pz = pz;
         l.off = (int)pl.tiles.size();
+        std::vector<int64_t> zs(zseg.size(), 0);  // slab cells of each z segment
+        for (size_t q = 0; q < zseg.size(); ++q)
+            for (int k = zseg[q].start; k < zseg[q].end; ++k) zs[q] += inslab(nz, zlohi[0], zlohi[1], k);
         std::vector<Range> xr;
         std::vector<char> xslab;
         auto put = [&](int lo, int hi, bool sl) {
@@ -87,7 +90,9 @@ void wave3d_plan(int nx, int ny, int nz, const Fused3DCfg &c, const int *xlohi, 
         put(xh, nx, true);
         // y rows are classified in groups of 8 (the interior band height);
         // the slab launch splits its groups into bands of RB rows
-        for (size_t q = 0; q < xr.size(); ++q)
+        for (size_t q = 0; q < xr.size(); ++q) {
+            int64_t xs = 0;
+            for (int i = xr[q].a; i < xr[q].b; ++i) xs += inslab(nx, xlohi[0], xlohi[1], i);
             for (int g0 = 0; g0 < ny; g0 += 8) {
                 bool ys = false;
                 for (int j = g0 - 1; j < g0 + 8 && j < ny; ++j) ys = ys || inslab(ny, ylohi[0], ylohi[1], j);
@@ -95,20 +100,19 @@ void wave3d_plan(int nx, int ny, int nz, const Fused3DCfg &c, const int *xlohi, 
                 for (int j0 = g0; j0 < std::min(g0 + 8, ny); j0 += RB) {
                     const int rows = std::min(RB, ny - j0);
                     const int64_t xn = xr[q].b - xr[q].a;
-                    int64_t xs = 0, ysn = 0;
-                    for (int i = xr[q].a; i < xr[q].b; ++i) xs += inslab(nx, xlohi[0], xlohi[1], i);
+                    int64_t ysn = 0;
                     for (int j = j0; j < j0 + rows; ++j) ysn += inslab(ny, ylohi[0], ylohi[1], j);
-                    for (const ZSeg &z : zseg) {
+                    for (size_t s = 0; s < zseg.size(); ++s) {
+                        const ZSeg &z = zseg[s];
                         pl.tiles.push_back(Tile3{xr[q].a, xr[q].b, j0, z.base, z.end, z.start, rows, 1});
                         const int64_t zn = z.end - z.start;
-                        int64_t zs = 0;
-                        for (int k = z.start; k < z.end; ++k) zs += inslab(nz, zlohi[0], zlohi[1], k);
                         l.cells += xn * rows * zn;
                         // four psi per slab a cell lies in
-                        l.psi += 4 * (xs * rows * zn + xn * ysn * zn + xn * rows * zs);
+                        l.psi += 4 * (xs * rows * zn + xn * ysn * zn + xn * rows * zs[s]);
                     }
                 }
             }
+        }
         if (pl.tiles.size() == (size_t)l.off) return;
         while ((pl.tiles.size() - (size_t)l.off) % 8) pl.tiles.push_back(Tile3{0, 0, 0, 0, 0, 0, 0, 0});
         l.n = (int)pl.tiles.size() - l.off;

@@ -365,11 +365,25 @@ void Sim::build_probe_tiles() {
     // leaves the cache empty, and every stepping call rebuilds before it
     // launches; each list is uploaded before its predecessor is released
     pt_ntiles = -1;
+    // the tile lists stay where only the probes are new
+    const std::array<int, 6> key = {vm, a, b, c3, kcfg.tile[3], wg2d() ? 1 : 0};
+    const bool plan = key != plan_key;
+    if (plan) plan_key[0] = -1;
     auto swap_in = [&](auto *&slot, auto *fresh) {
         al.put(slot);
         slot = fresh;
     };
-    if (ndim == 2) {
+    // a list's three arrays in one block, at `start`
+    auto lists_in = [&](int *&start, int *&cell, int *&slot, const std::vector<int> &s, const std::vector<int> &c,
+                        const std::vector<int> &l) {
+        std::vector<int> h(s);
+        h.insert(h.end(), c.begin(), c.end());
+        h.insert(h.end(), l.begin(), l.end());
+        swap_in(start, dev_upload(al, h.data(), h.size(), st));
+        cell = start + s.size();
+        slot = cell + c.size();
+    };
+    if (ndim == 2 && plan) {
         const Fused2DCfg c = single2d();
         const int xl[2] = {ax[0].lo, ax[0].hi}, yl[2] = {ax[1].lo, ax[1].hi};
         const int nt = fused2d_ntiles(nx, ny, c);
@@ -380,7 +394,7 @@ void Sim::build_probe_tiles() {
         ids.insert(ids.end(), outer.begin(), outer.end());
         swap_in(tl2_dev, dev_upload(al, ids.data(), std::max<size_t>(ids.size(), 1), st));
     }
-    if (ndim == 3) {
+    if (ndim == 3 && plan) {
         const int xl[2] = {ax[0].lo, ax[0].hi}, yl[2] = {ax[1].lo, ax[1].hi}, zl[2] = {ax[2].lo, ax[2].hi};
         if (flat3d()) {
             plan3.tiles.clear();
@@ -450,9 +464,7 @@ void Sim::build_probe_tiles() {
         start[(size_t)tile[order[q]] + 1]++;
     }
     for (int t = 0; t < ntiles; ++t) start[(size_t)t + 1] += start[(size_t)t];
-    swap_in(pt_start, dev_upload(al, start.data(), start.size(), st));
-    swap_in(pt_cell, dev_upload(al, cell.data(), std::max<size_t>(cell.size(), 1), st));
-    swap_in(pt_slot, dev_upload(al, slot.data(), std::max<size_t>(slot.size(), 1), st));
+    lists_in(pt_start, pt_cell, pt_slot, start, cell, slot);
     if (ndim == 3 && kcfg.variant == 3) {
         // which slab tiles record probes (a probe cell in their own planes
         // and rows), so that the others skip the group look-ups
@@ -511,35 +523,39 @@ void Sim::build_probe_tiles() {
     pt_cfg[4] = vm;
     pt_cfg[5] = kcfg.tile[3];
     if (wg2d()) {
-        const int xl[2] = {ax[0].lo, ax[0].hi}, yl[2] = {ax[1].lo, ax[1].hi};
-        std::vector<TileW> tl;
-        if (kcfg.variant == 4) {
-            wg2d_default({{nx, ny}}, wmat(), cus, wg_cls, wg_tb);
-        } else {
-            wg_cls = kcfg.tile[1];
-            wg_tb = kcfg.tile[2];
+        if (plan) {
+            const int xl[2] = {ax[0].lo, ax[0].hi}, yl[2] = {ax[1].lo, ax[1].hi};
+            if (kcfg.variant == 4) {
+                wg2d_default({{nx, ny}}, wmat(), cus, wg_cls, wg_tb);
+            } else {
+                wg_cls = kcfg.tile[1];
+                wg_tb = kcfg.tile[2];
+            }
+            wg_mat = wmat();
+            wg_list.clear();
+            wg2d_plan(0, nx, ny, wg_cls, wg_mat, wg_tb, xl, yl, wg_list);
+            wg_n = (int)wg_list.size();
+            swap_in(wg_dev, dev_upload(al, wg_list.data(), wg_list.size(), st));
         }
-        wg_mat = wmat();
-        wg2d_plan(0, nx, ny, wg_cls, wg_mat, wg_tb, xl, yl, tl);
-        wg_n = (int)tl.size();
-        swap_in(wg_dev, dev_upload(al, tl.data(), tl.size(), st));
         std::vector<WgProbe> pr;
         for (size_t q = 0; q < probe_cells.size(); ++q)
             pr.push_back(WgProbe{0, (int)(probe_cells[q] / ny), (int)(probe_cells[q] % ny), (int)q});
         std::vector<int> st2, ce, sl;
-        wg2d_probes(tl, 0, pr, st2, ce, sl);
-        swap_in(pt2_start, dev_upload(al, st2.data(), st2.size(), st));
-        swap_in(pt2_cell, dev_upload(al, ce.data(), std::max<size_t>(ce.size(), 1), st));
-        swap_in(pt2_slot, dev_upload(al, sl.data(), std::max<size_t>(sl.size(), 1), st));
+        wg2d_probes(wg_list, 0, pr, st2, ce, sl);
+        lists_in(pt2_start, pt2_cell, pt2_slot, st2, ce, sl);
     } else if (ndim == 2 && kcfg.variant == 3) {
         const int V = kcfg.tile[0], TX = kcfg.tile[1], TB = kcfg.tile[2];
-        const int xl[2] = {ax[0].lo, ax[0].hi}, yl[2] = {ax[1].lo, ax[1].hi};
-        std::vector<Tile2T> in, out;
-        tb2d_plan(0, nx, ny, V, TB, TX, kcfg.tile[3], xl, yl, in, out);
-        tb2_inner = (int)in.size();
-        tb2_outer = (int)out.size();
-        in.insert(in.end(), out.begin(), out.end());
-        swap_in(tb2_dev, dev_upload(al, in.data(), std::max<size_t>(in.size(), 1), st));
+        if (plan) {
+            const int xl[2] = {ax[0].lo, ax[0].hi}, yl[2] = {ax[1].lo, ax[1].hi};
+            std::vector<Tile2T> out;
+            tb2_list.clear();
+            tb2d_plan(0, nx, ny, V, TB, TX, kcfg.tile[3], xl, yl, tb2_list, out);
+            tb2_inner = (int)tb2_list.size();
+            tb2_outer = (int)out.size();
+            tb2_list.insert(tb2_list.end(), out.begin(), out.end());
+            swap_in(tb2_dev, dev_upload(al, tb2_list.data(), std::max<size_t>(tb2_list.size(), 1), st));
+        }
+        const std::vector<Tile2T> &in = tb2_list;
         // probe groups by position in the list: the tile starting at or
         // last before the probe's row in its strip
         const int ow = tb2d_own(V, TB), nstrip = (ny + ow - 1) / ow;
@@ -562,10 +578,9 @@ void Sim::build_probe_tiles() {
             st2[(size_t)tl[ord[q]] + 1]++;
         }
         for (size_t t = 0; t < in.size(); ++t) st2[t + 1] += st2[t];
-        swap_in(pt2_start, dev_upload(al, st2.data(), st2.size(), st));
-        swap_in(pt2_cell, dev_upload(al, ce.data(), std::max<size_t>(ce.size(), 1), st));
-        swap_in(pt2_slot, dev_upload(al, sl.data(), std::max<size_t>(sl.size(), 1), st));
+        lists_in(pt2_start, pt2_cell, pt2_slot, st2, ce, sl);
     }
+    plan_key = key;
     pt_ntiles = ntiles;
 }
 

@@ -145,6 +145,9 @@ struct Sim {
     // tile[1] = size class, tile[2] = most steps per pass; variant 4): the
     // tile list and its probe groups (pt2_*)
     TileW *wg_dev = nullptr;
+    std::vector<TileW> wg_list;     // host copies of the 2D lists
+    std::vector<Tile2T> tb2_list;
+    std::array<int, 6> plan_key{{-1}};  // what the tile lists were made for
     int wg_n = 0, wg_cls = 0, wg_tb = 1, wg_mat = -1;
     bool wg2d() const {
         return ndim == 2 && !is_graph && ((kcfg.variant == 3 && kcfg.tile[0] == 64) || (kcfg.variant == 4 && res2d_ok()));
