@@ -1059,6 +1059,14 @@ int default_variant_tiles(const Sim &s, fdtd_kernel_config &k) {
             k.variant = two ? 3 : 2;
             k.tile[0] = c.V;
             if (c.V == 4 && s.ncell > kFlatMaxCells4 && s.ncell < kTwoStepMinCells) k.tile[2] = kMarchMidTX;
+            // few planes without a layer: one chunk takes them all, and the
+            // marching kernel's workgroups fill the device (us per step, one
+            // thread per cell against it: 3x816x816 20.6, 19.0; 5x836x836
+            // 35.4, 31.5; 8x661x660 36.1, 33.6; with 222 workgroups,
+            // 8x591x588, and with a layer no faster: 29.3, 29.3; 48, 78)
+            const bool layer = s.ax[0].lo + s.ax[0].hi + s.ax[1].lo + s.ax[1].hi + s.ax[2].lo + s.ax[2].hi > 0;
+            const int64_t wgs = (int64_t)((s.ny + 7) / 8) * ((s.nz + 255) / 256);
+            if (c.V == 4 && !two && !layer && s.nx <= 8 && wgs >= 240) k.tile[2] = 16;
             return 0;
         }
     }
