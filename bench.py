@@ -164,19 +164,23 @@ def bench_2d(args, steps=10000):
     if lg > 2 * gs:  # the CSR sweep: what its format must move (runs of rows move less)
         out["graph_form"]["impl_bytes_per_cell_update"] = csr_impl_bytes(pb) / pb.cells
     g.close()
-    # frequency-domain monitor: Ez on the central 2048^2 box at 4 frequencies
-    # (single steps while it is set), against single steps without it
+    # frequency-domain monitor: Ez on the central 2048^2 box at 4 frequencies,
+    # in the single-step kernel with and without it, and in the default
+    # workgroup tiles (which store the samples of every step of a pass)
     ms = 400
     m = Sim.from_problem(pb)
     m.set_kernel(2, (2, 4))
     tp, _, _ = timed_steps(m, ms, 5)
     m.set_dft("ez", (1024, 1024), (3072, 3072), [0.5e9, 1.0e9, 1.5e9, 2.0e9])
     tm, _, _ = timed_steps(m, ms, 5)
+    m.set_kernel(0)
+    td, _, _ = timed_steps(m, ms, 5)
     m.close()
     out["dft_monitor"] = dict(steps=ms, box_cells=2048 * 2048, frequencies=4,
                               single_step_gcells_per_s=pb.cells * ms / tp / 1e9,
                               with_monitor_gcells_per_s=pb.cells * ms / tm / 1e9,
-                              monitor_us_per_step=(tm - tp) / ms * 1e6)
+                              monitor_us_per_step=(tm - tp) / ms * 1e6,
+                              default_with_monitor_gcells_per_s=pb.cells * ms / td / 1e9)
     # the paper's split-field PML (two-pass reference kernels), against the
     # CPML through the same kernels, and its 4-node explicit graph
     import dataclasses

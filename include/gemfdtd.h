@@ -170,9 +170,10 @@ int fdtd_set_source_box(fdtd_sim *sim, int component, const int32_t *lo, const i
  * t_n = (n+1) dt for an E component and (n+1/2) dt for an H component (the
  * sample's time on the leapfrog grid), summed in FP64.  nf in [0, 16]; a
  * call replaces the monitor (nf = 0 removes it).  While a monitor is set,
- * fdtd_step advances one step per pass (the multi-step kernels do not keep
- * the intermediate steps), and fdtd_step_profile, fdtd_autotune and
- * fdtd_adjoint_eps return FDTD_ESTATE; fdtd_reset zeroes the sums.
+ * 2D workgroup tiles store the samples of every step of a pass; the other
+ * multi-step kernels keep no intermediate step, so fdtd_step advances one
+ * step per pass where they are selected.  fdtd_step_profile, fdtd_autotune
+ * and fdtd_adjoint_eps return FDTD_ESTATE; fdtd_reset zeroes the sums.
  * FDTD_EINVAL for a bad box, component or frequency. */
 int fdtd_set_dft(fdtd_sim *sim, int component, const int32_t *lo, const int32_t *hi, int32_t nf,
                  const double *freqs);
@@ -394,8 +395,9 @@ int fdtd_step_profile(fdtd_sim *sim, int32_t steps, fdtd_launch_stat *out, int32
 
 /* --------------------------------------------------------------------- */
 /* Batched form: many independent 2D problems of different sizes advanced  */
-/* together, one launch per time block over a packed arena, captured in a  */
-/* HIP graph.                                                              */
+/* together: one list of tiles over all problems, one launch per pass      */
+/* (with the wavefront tiles, two per group of one vector width, captured  */
+/* in a HIP graph).                                                        */
 /* --------------------------------------------------------------------- */
 typedef struct fdtd_batch fdtd_batch;
 
@@ -415,9 +417,10 @@ int fdtd_batch_step(fdtd_batch *b, int64_t n);
  * CPML slab (0 = tx).  The default, 4, 16, 1, 0, stands for the library's
  * own choice: the workgroup tiles of fdtd_kernel_config's variant 3 over all
  * problems in one launch per pass of up to 10-14 steps (the wavefront tiles
- * of these values where a problem's rows are too long for them).
- * Synchronises; the state is kept.  FDTD_EINVAL for other values (the configuration is then
- * unchanged). */
+ * of these values where a problem's rows are too long for them); 4, 16, 1,
+ * 16 asks for the wavefront tiles with the same rows everywhere.
+ * Synchronises; the state is kept.  FDTD_EINVAL for other values (the
+ * configuration is then unchanged). */
 int fdtd_batch_set_kernel(fdtd_batch *b, int32_t tb, int32_t tx, int32_t vmax, int32_t txo);
 /* Autotuner of the batch: time every candidate configuration of
  * fdtd_batch_set_kernel (tb in {4, 2}, tx in {8, 16, 32}, vmax in {1, 2,

@@ -27,7 +27,7 @@
 // step with CPML against the default before (single steps below 1.5 M
 // cells, four-step marching passes above): 250^2 1.18 (6.3), 400^2 1.43
 // (7.4), 1024^2 2.42 (9.5), 2048^2 4.8 (17.3), 4096^2 14.3 (41.5; with a Ca
-// map 17.8 against 44.0), 6400^2 32.5 (80.9).  Tiles of 176 rows in two
+// map 15.6 against 44.0), 6400^2 32.5 (80.9).  Tiles of 176 rows in two
 // workgroups per CU were as fast at 4096^2 (15.6) and slower below (2048^2
 // 5.8); 16 wavefronts of 2 or 4 rows no faster than 8 of 4 or 8.
 //

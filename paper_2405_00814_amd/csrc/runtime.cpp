@@ -865,7 +865,9 @@ int64_t Sim::graph_advance(int64_t n) {
 // n steps: pairs through the two-step pass where it is selected, single
 // steps otherwise
 void Sim::advance(int64_t n) {
-    // a frequency-domain monitor needs every step's field: single steps
+    // a frequency-domain monitor needs every step's field: the tiles store
+    // their samples of each step; the other multi-step kernels keep none, so
+    // single steps are taken in their place
     const bool mon = dft.comp >= 0;
     const bool two = kcfg.variant == 3 && ndim == 3 && !is_graph && !mon;
     const bool wg = wg_pass(n) > 0;
@@ -992,10 +994,13 @@ void Sim::refold(int64_t c0, int64_t c1) {
     hip_check(hipStreamSynchronize(st), "sync");
 }
 
-// 2D defaults (measured on MI355X over grids of 256^2 .. 6400^2): single
-// steps below 1.5M cells (one column per lane below 8M cells, two above),
-// four steps per pass from 1.5M cells on with one column per lane (two were
-// 10-20 % slower at every size) and the row chunk from tb2d_default_tx.
+// 2D defaults: workgroup tiles (us per step against the kernels below, best
+// of them: 250^2 1.2 and 6.3, 1024^2 2.4 and 9.5, 4096^2 14.3 and 41.5).
+// Grids they do not take (rows of more than 2^20 cells; fewer than 40 rows
+// and 1.5M cells or more): single steps below 1.5M cells (one column per
+// lane below 8M cells, two above), four steps per marching pass above, with
+// one column per lane (two were 10-20 % slower at every size) and the row
+// chunk from tb2d_default_tx.
 constexpr int64_t kTB2MinCells = (int64_t)3 << 19;
 constexpr int64_t kWide2DCells = (int64_t)8 << 20;
 constexpr int kTB2DefaultTX = 4;
@@ -1082,7 +1087,7 @@ static bool config_ok(const Sim &s, const fdtd_kernel_config &k) {
     if (k.tb != 0 && k.tb != 1 && !graph_tb) return false;
     if (k.variant == 1) return true;
     if (s.split) return false;
-    if (k.variant == 4)  // whole grid in one workgroup: checked again (probes) at every step call
+    if (k.variant == 4)  // small closed grids in workgroup tiles: checked again (probes) at every step call
         return s.ndim == 2 && !s.is_graph && k.tile[0] == 0 && k.tile[1] == 0 && k.tile[2] == 0 &&
                k.tile[3] == 0 && s.res2d_ok();
     if (k.variant != 2 && k.variant != 3) return false;

@@ -405,7 +405,8 @@ class Batch:
 
     def set_kernel(self, tb=4, tx=16, vmax=2, txo=0):
         """Steps per pass (1, 2, 4), rows per tile, widest column vector,
-        rows per tile near a CPML slab (0: tx)."""
+        rows per tile near a CPML slab (0: tx), of the wavefront tiles;
+        (4, 16, 1, 0) is the library's own choice, workgroup tiles."""
         L.call("fdtd_batch_set_kernel", self.h, int(tb), int(tx), int(vmax), int(txo))
 
     def autotune(self, trial_steps=64):
