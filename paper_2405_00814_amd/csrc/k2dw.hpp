@@ -19,15 +19,17 @@
 // What bounds it: on small grids the latency of a dependent launch (3.6 us)
 // and of the tile's loads (about 3 us), spread over the steps of the pass,
 // then 0.35-0.55 us per step (VALU of one CU and a barrier); on large grids
-// the pass's memory traffic (the state once, plus the halo) and the VALU
-// about equally.  The marching kernel (k2dt.hip) moves the state of every
-// row through a pipeline of register copies and executes about 32 VALU
+// the VALU (counters, 4096^2 with a Ca map: busy 0.73 of the launch, its
+// wavefronts 0.21 of their time waiting for memory, LDS or barriers, 0.47
+// to issue; 4.0 TB/s).  The marching kernel (k2dt.hip) moves the state of
+// every row through a pipeline of register copies and executes about 32 VALU
 // instructions per cell and step besides its halo; here a cell and step
-// costs 9 (interior, no Ca map), because nothing moves.  Measured, us per
+// costs 9 in the step loop (interior, no Ca map; 11.7 over the whole launch
+// with one, loads, stores and layers counted), because nothing moves.  Measured, us per
 // step with CPML against the default before (single steps below 1.5 M
 // cells, four-step marching passes above): 250^2 1.18 (6.3), 400^2 1.43
 // (7.4), 1024^2 2.42 (9.5), 2048^2 4.8 (17.3), 4096^2 14.3 (41.5; with a Ca
-// map 15.6 against 44.0), 6400^2 32.5 (80.9).  Tiles of 176 rows in two
+// map 15.5 against 44.0), 6400^2 32.5 (80.9).  Tiles of 176 rows in two
 // workgroups per CU were as fast at 4096^2 (15.6) and slower below (2048^2
 // 5.8); 16 wavefronts of 2 or 4 rows no faster than 8 of 4 or 8.
 //

@@ -10,8 +10,10 @@
 // (k3dw.hip) reads each value once from memory but walks its planes in a
 // dependent chain: on a grid of 10^5 - 10^7 cells its few workgroups leave
 // the chip idle.  Bound by the launch (4 us), then by the latency and rate
-// of about 40 cached loads per thread, 90 with CPML: 100x90x84 with 10-cell
-// CPML 19 us per step (118 before), 100^3 without 11 (42).  More wavefronts
+// of about 40 cached loads per thread (59 on average on 100x90x84 with
+// 10-cell CPML, up to 90 in its corners; counters there: VALU busy 0.42 of
+// the launch, 580 instructions per cell, 0.44 of a wavefront's time waiting):
+// 19 us per step (118 before), 100^3 without CPML 11 (42).  More wavefronts
 // per SIMD at fewer registers spilled and were slower (5: 22 us, 6: 37).
 //
 // CPML: the values a wavefront needs of an axis' slabs (psi, b, c,

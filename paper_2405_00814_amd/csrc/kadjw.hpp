@@ -16,8 +16,11 @@
 // message gy of the row below its last one and, with its own copies of Hy,
 // psi and Db, ex of the row above its first.
 //
-// Bound by VALU and latency as the forward tiles.  Measured beside the
-// recompute's launches, 1024^2 with CPML and 256^2 design cells: 7.2 us per
+// Bound by latency at few wavefronts: 176 registers leave a CU one workgroup
+// of eight wavefronts, and 1024^2 with CPML makes 536 of them, two full
+// rounds of the 256 CUs and a third of 24 (counters: VALU busy 0.33 of the
+// launch, 4.2 wavefronts resident per CU, 0.39 of their time waiting).
+// Measured beside the recompute's launches there, 256^2 design cells: 7.2 us per
 // step in passes of 8 (13.2 with one step per launch, k_adj_fused); 16
 // wavefronts of 4 rows instead of 8 of 8 were 8 % faster there and 4 %
 // slower at 2048^2.
